@@ -82,16 +82,7 @@ __device__ __forceinline__ StepOut step(State& s, uint32_t n, uint32_t rep, uint
         uy = s.spare_y;
     }
     const float rx = signed_unit(ux), ry = signed_unit(uy);
-    const float gg = s.gx * s.gx + s.gy * s.gy;
-    const float t = gg > 0.0f ? div_sqrt_rn(rc.Q, gg) : 0.0f;  // Q = 1 - persistence: 0 or in [2^-24, 1]
-    const float wx = (rc.per * s.dx - t * s.gx) + rc.rnd * rx;
-    const float wy = (rc.per * s.dy - t * s.gy) + rc.rnd * ry;
-    const float ww = wx * wx + wy * wy;
-    if (ww > 0.0f) {
-        const float inv = div_sqrt_rn(1.0f, ww);
-        s.dx = wx * inv;
-        s.dy = wy * inv;
-    }
+    steer(s.dx, s.dy, s.gx, s.gy, rc.per, rc.Q, rc.rnd, rx, ry);
     o.x1 = s.x + rc.L * s.dx;
     o.y1 = s.y + rc.L * s.dy;
     // Every lane runs the whole step and the outcome selects what it keeps (no branch per outcome, so the
@@ -101,12 +92,8 @@ __device__ __forceinline__ StepOut step(State& s, uint32_t n, uint32_t rep, uint
     const bool inb = fc1 >= 0.0f && fc1 < (float)W && fr1 >= 0.0f && fr1 < (float)H;
     const Sample s1 = sample(dem, o.x1, o.y1);
     const float dz = s.z - s1.z;
-    // dl2 + dz^2 >= dl2: with dl2 >= 2^-96 (a run constant) no lane needs the small-argument check
-    float ds;
-    if (rc.dl2 >= 0x1p-96f)
-        ds = sqrt_rn_big(rc.dl2 + dz * dz);
-    else
-        ds = sqrt_rn(rc.dl2 + dz * dz);
+    // dl2 + dz^2 >= dl2: with dl2 >= 2^-96 (a run constant) no lane is below the short form's range
+    const float ds = sqrt_rn(rc.dl2 + dz * dz, rc.dl2 >= 0x1p-96f);
     const float num = s.v2 + g2 * (dz - rc.mdl);
     const bool pos = num > 0.0f;
     const float aa = rc.cd * ds;

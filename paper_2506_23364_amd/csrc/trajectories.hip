@@ -490,29 +490,15 @@ void k_trajectories(TrajArgs a) {
                     uy = spare_y;
                 }
                 const float rx = signed_unit(ux), ry = signed_unit(uy);
-                const float gg = gx * gx + gy * gy;
-                // Q = 1 - persistence is 0 or in [2^-24, 1] (persistence in [0, 1])
-                const float t = gg > 0.0f ? div_sqrt_rn(R.Q, gg) : 0.0f;
-                const float wx = (R.per * dx - t * gx) + R.rnd * rx;
-                const float wy = (R.per * dy - t * gy) + R.rnd * ry;
-                const float ww = wx * wx + wy * wy;
-                if (ww > 0.0f) {
-                    const float inv = div_sqrt_rn(1.0f, ww);
-                    dx = wx * inv;
-                    dy = wy * inv;
-                }
+                steer(dx, dy, gx, gy, R.per, R.Q, R.rnd, rx, ry);
                 const float x1 = x + R.L * dx;
                 const float y1 = y + R.L * dy;
                 const float fc1 = floorf(x1), fr1 = floorf(y1);
                 const bool inb = !lim && fc1 >= 0.0f && fc1 < fW && fr1 >= 0.0f && fr1 < fH;
                 const Sample s1 = bilinear_pad(dem_rs, Wp, row_bytes, x1, y1);
                 const float dz = z - s1.z;
-                // dl2 + dz^2 >= dl2: with dl2 >= 2^-96 (a run constant) no lane needs the small-argument check
-                float ds;
-                if (R.dl2 >= 0x1p-96f)
-                    ds = sqrt_rn_big(R.dl2 + dz * dz);
-                else
-                    ds = sqrt_rn(R.dl2 + dz * dz);
+                // dl2 + dz^2 >= dl2: with dl2 >= 2^-96 (a run constant) no lane is below the short form's range
+                const float ds = sqrt_rn(R.dl2 + dz * dz, R.dl2 >= 0x1p-96f);
                 const float num = v2 + a.g2 * (dz - R.mdl);
                 bool stop = !(num > 0.0f);
                 const float v2n = num / (1.0f + R.cd * ds);
