@@ -144,25 +144,34 @@ __device__ __forceinline__ Sample bilinear(const float* __restrict__ dem, int H,
 // row_bytes = 4 Wp) through a buffer resource: for (x, y) inside the grid the corner (floor(x - 1/2),
 // floor(y - 1/2)) lies in [-1, W - 1] x [-1, H - 1], i.e. inside the padded grid, and the border holds
 // exactly the clamped texels, so the four values and the arithmetic are those of bilinear().
-__device__ __forceinline__ Sample bilinear_pad(__amdgpu_buffer_rsrc_t rs, uint32_t Wp, uint32_t row_bytes, float x,
-                                               float y) {
+// In two parts, so that work that does not need the heights can run while they are on their way.
+struct PatchLoad {
+    float a, b, c, d, fx, fy;
+};
+__device__ __forceinline__ PatchLoad bilinear_pad_load(__amdgpu_buffer_rsrc_t rs, uint32_t Wp, uint32_t row_bytes, float x,
+                                                       float y) {
     const float sx = x - 0.5f, sy = y - 0.5f;
     const float fc = floorf(sx), fr = floorf(sy);
-    const float fx = sx - fc, fy = sy - fr;
     const uint32_t off = (__umul24((uint32_t)((int)fr + 1), Wp) + (uint32_t)((int)fc + 1)) * 4u;
     // two 8-byte loads (the raw words of a, b and of c, d), both issued before either is used
     const auto ab = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
     const auto cd = __builtin_amdgcn_raw_buffer_load_b64(rs, off, row_bytes, 0);
     __builtin_amdgcn_sched_barrier(0);  // keep both loads ahead of their uses (one memory latency, not two)
-    const float a = __uint_as_float(ab[0]), b = __uint_as_float(ab[1]);
-    const float c = __uint_as_float(cd[0]), d = __uint_as_float(cd[1]);
-    const float top = a + fx * (b - a);
-    const float bot = c + fx * (d - c);
+    return PatchLoad{__uint_as_float(ab[0]), __uint_as_float(ab[1]), __uint_as_float(cd[0]), __uint_as_float(cd[1]),
+                     sx - fc, sy - fr};
+}
+__device__ __forceinline__ Sample bilinear_pad_value(const PatchLoad& p) {
+    const float top = p.a + p.fx * (p.b - p.a);
+    const float bot = p.c + p.fx * (p.d - p.c);
     Sample s;
-    s.z = top + fy * (bot - top);
-    s.gx = (b - a) + fy * ((d - c) - (b - a));
+    s.z = top + p.fy * (bot - top);
+    s.gx = (p.b - p.a) + p.fy * ((p.d - p.c) - (p.b - p.a));
     s.gy = bot - top;
     return s;
+}
+__device__ __forceinline__ Sample bilinear_pad(__amdgpu_buffer_rsrc_t rs, uint32_t Wp, uint32_t row_bytes, float x,
+                                               float y) {
+    return bilinear_pad_value(bilinear_pad_load(rs, Wp, row_bytes, x, y));
 }
 
 // buffer resource over `bytes` bytes at p (gfx9 descriptor word 3: 32-bit data format)

@@ -13,9 +13,11 @@
 //    so consecutive slots start at the same or neighbouring cells and their paths share most cells.
 //  - Device-scope atomics on the rasters are performed beyond L2 (at the memory side), so they are the
 //    cost to cut. Entry counts and per-cell max v^2 go first into a table in LDS shared by the whole
-//    workgroup (tag, count, max; linear probing), flushed to the rasters at epoch boundaries (a pair of
-//    barriers every kFlush iterations per wave on average). A cell whose probes are all held by other
-//    cells goes straight to the raster.
+//    workgroup (tag, count, max; two buckets of four slots per cell), flushed to the rasters at epoch boundaries
+//    (a pair of barriers every kFlush iterations per wave on average). A cell whose candidate slots are all
+//    held by other cells goes straight to the raster. A visit that ended is accumulated in the next iteration,
+//    while that iteration's heights are on their way, so the table's LDS round trips are hidden behind the
+//    gather (3 % of the large passes).
 //  - An epoch is a budget of kFlush x (waves per block) wave-iterations that the block's waves claim one
 //    at a time from an LDS counter, so a wave that runs faster than its neighbours does more of them and
 //    every wave reaches the boundary within about one iteration of the others (a fixed count per wave
@@ -48,6 +50,13 @@ __device__ __forceinline__ uint32_t lds_ld(uint32_t* p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// four consecutive words of a table in LDS, 16-byte aligned, in one read
+__device__ __forceinline__ u32x4 lds_ld4(const uint32_t* p) {
+    return *(const volatile __attribute__((address_space(3))) u32x4*)(const __attribute__((address_space(3))) uint32_t*)p;
+}
+
 // A raster cell's v^2 bits as this CU's caches hold them: a workgroup-scope read, served by L1 or the XCD's
 // L2 when they hold the line. The raster's maxima are performed at the memory side, so the cached value can
 // be older than the memory's, but every value the cell takes during the pass is at least the one before
@@ -68,7 +77,7 @@ __device__ __forceinline__ void global_max(uint32_t* __restrict__ p, uint32_t bi
 using namespace dev;
 
 // Workgroup-shared accumulation table: kTbl slots of (cell key, entry count, max v^2 bits) in LDS,
-// open addressing with a few linear probes. A particle's visit to a cell (from its entry, or its release,
+// eight candidate slots per cell. A particle's visit to a cell (from its entry, or its release,
 // to the step that leaves the cell or ends the path) goes into the table once, when it ends: one entry
 // and the visit's largest v^2 (the counts are the same as counting each entry when it happens, and one
 // table operation per visit replaces a claim at the entry plus a max at the exit). Slots are emptied only
@@ -78,7 +87,9 @@ using namespace dev;
 // (low) and their number at the last boundary (high).
 template <int kTbl>
 struct Table {
-    uint32_t tag[kTbl], cnt[kTbl], vmx[kTbl];
+    // a bucket is four consecutive slots: one 16-byte read shows a key's four candidates
+    alignas(16) uint32_t tag[kTbl];
+    uint32_t cnt[kTbl], vmx[kTbl];
 };
 
 // Workgroup control block in LDS. The window is a range of consecutive slots that the workgroup's waves
@@ -103,7 +114,7 @@ struct Control {
 // kWpe: waves per SIMD the register budget is sized for (8: 64 VGPRs; 6: 80).
 // kRec: the recording instantiation (single run): the particles of the recorded range also write their
 // points and end records (a diagnostic; the other instantiations compile none of it).
-template <bool kBatch, bool kAlpha, int kBlock, int kFlush, int kTbl, int kProbes, int kWindow, int kKeep, int kWpe = 8,
+template <bool kBatch, bool kAlpha, int kBlock, int kFlush, int kTbl, int kWindow, int kKeep, int kWpe = 8,
           bool kRec = false>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kWpe)))
 void k_trajectories(TrajArgs a) {
@@ -116,6 +127,7 @@ void k_trajectories(TrajArgs a) {
     constexpr uint32_t kSuper = (uint32_t)kWindow * kBlock;  // slots per window top-up
     static_assert(kTbl % kBlock == 0, "every thread flushes the same number of table slots");
     constexpr int kPer = kTbl / kBlock;
+    constexpr uint32_t kBuckets = (uint32_t)kTbl / 4u;
     __shared__ Table<kTbl> tb;
     __shared__ Control ctl;
     const int lane = threadIdx.x & (kWave - 1);
@@ -159,39 +171,68 @@ void k_trajectories(TrajArgs a) {
         }
     };
 
-    // table slot of `key`, claimed if a probe finds an empty slot first; -1 if every probe is held by
-    // another cell. Within an epoch slots are only filled, never emptied, so a key's first probe that is
-    // empty or holds it is the same for every lane. (A retained key can find an earlier probe emptied at
-    // the boundary and take that one as well: two slots of one cell, both flushed, the sums unchanged.)
-    // The probes' tags are read in groups of kGroup, one LDS round trip per group, and the group's slots
-    // are then taken in probe order: a read that shows the key is final (only the key's own claim writes
-    // it), one that shows another key stays true (slots are not emptied within an epoch), and one that shows
-    // an empty slot is settled by the compare-and-swap. So the slot taken is the first in probe order that
-    // is empty or holds the key, as with one probe at a time, but a claim no longer waits for up to kProbes
-    // dependent round trips.
+    // Table slot of `key`, claimed if a candidate is empty; -1 if all of them are held by other cells. The candidates are
+    // the four slots of the key's bucket, then those of a second bucket. A bucket's tags come in one 16-byte read: one
+    // that shows the key is final within the epoch (only the key's own claim writes it, and slots are emptied only at a
+    // boundary), and an empty one is settled by the compare-and-swap. (A kept slot behind a newly emptied one can give
+    // a cell a second slot: both are flushed, the sums and maxima unchanged.) Two buckets of four overflow less than
+    // eight slots in a row, and all candidates of a bucket are seen in one LDS round trip (8192^2 pass 9.2 -> 8.7 ms).
+    auto bucket = [&](uint32_t key, uint32_t mul) -> uint32_t {
+        // multiplicative hash modulo 2^24 with full-rate 24-bit products; the key's low 24 bits spread one block's cells
+        return (__umul24((__umul24(key, mul) >> 8) & 0xFFFFu, kBuckets) >> 16) * 4u;
+    };
+    auto first_of = [&](const u32x4& t, uint32_t v) -> int {
+        int e = -1;
+#pragma unroll
+        for (int i = 3; i >= 0; --i) e = t[i] == v ? i : e;
+        return e;
+    };
     auto claim = [&](uint32_t key) -> int {
-        constexpr int kGroup = 4;
-        const uint32_t h = (uint32_t)(((uint64_t)(key * 0x9E3779B1u) * (uint64_t)kTbl) >> 32);
-#pragma unroll
-        for (int g = 0; g < kProbes; g += kGroup) {
-            uint32_t sl[kGroup], t[kGroup];
-#pragma unroll
-            for (int i = 0; i < kGroup && g + i < kProbes; ++i) {
-                sl[i] = h + (uint32_t)(g + i);
-                if (sl[i] >= (uint32_t)kTbl) sl[i] -= (uint32_t)kTbl;
-                t[i] = lds_ld(tb.tag + sl[i]);
-            }
-#pragma unroll
-            for (int i = 0; i < kGroup && g + i < kProbes; ++i) {
-                uint32_t ti = t[i];
-                if (ti == kEmpty) {
-                    const uint32_t old = atomicCAS(tb.tag + sl[i], kEmpty, key);
-                    ti = (old == kEmpty) ? key : old;
+        uint32_t at = bucket(key, 0x9E3779u);
+        u32x4 t = lds_ld4(tb.tag + at);
+        int i = first_of(t, key);
+        if (i < 0) {
+            // the common claim: the bucket's first empty slot, taken by this key
+            i = first_of(t, kEmpty);
+            uint32_t old = kEmpty;
+            if (i >= 0) old = atomicCAS(tb.tag + at + i, kEmpty, key);
+            if (i < 0 || (old != kEmpty && old != key)) {
+                const uint32_t first = at;
+                i = -1;
+#pragma unroll 1
+                for (int tries = 0; tries < 8; ++tries) {
+                    t = lds_ld4(tb.tag + at);
+                    i = first_of(t, key);
+                    if (i >= 0) break;
+                    i = first_of(t, kEmpty);
+                    if (i >= 0) {
+                        old = atomicCAS(tb.tag + at + i, kEmpty, key);
+                        if (old == kEmpty || old == key) break;
+                        i = -1;
+                    } else if (at == first) {
+                        at = bucket(key, 0xC2B2AEu) ^ 4u;
+                    } else {
+                        break;
+                    }
                 }
-                if (ti == key) return (int)sl[i];
             }
         }
-        return -1;
+        return i < 0 ? -1 : (int)at + i;
+    };
+    // The visit that ended in the wave's previous iteration: its cell and largest v^2.
+    uint32_t leave_key = kEmpty, leave_bits = 0;
+    auto accumulate = [&]() {
+        if (leave_key != kEmpty) {
+            const int sl = claim(leave_key);
+            if (sl >= 0) {
+                atomicAdd(tb.cnt + sl, 1u);
+                if (leave_bits) atomicMax(tb.vmx + sl, leave_bits);
+            } else {
+                atomicAdd(counts + leave_key, 1u);
+                if (leave_bits) global_max(vmax2 + leave_key, leave_bits);
+            }
+            leave_key = kEmpty;
+        }
     };
 
     // Shifts the window past the slots handed out in the epoch that ended and tops it up with a new
@@ -468,15 +509,13 @@ void k_trajectories(TrajArgs a) {
 
             // ---- one step of every live particle
             const RunConst& R = rc;
-            bool leave = false;  // a visit ended: its cell and largest v^2
-            uint32_t leave_bits = 0;
-            uint32_t leave_key = 0;
+            PatchLoad pl{};
+            float x1 = 0, y1 = 0;
             if (alive) {
                 // Every live lane runs the whole step and the outcome selects what it keeps: a lane at the
                 // step limit, leaving the grid or stopping discards its target (an off-grid target's gather
                 // reads through the buffer's bounds check, so it cannot fault). Without the nested branches
                 // the compiler no longer copies the particle state at every join (5 % of the alpine pass).
-                const bool lim = n >= a.S;
                 uint32_t ux, uy;
                 if ((it & 1) == 0) {  // n is even
                     // the key is wave-uniform: pinning it to scalar registers here makes the round keys
@@ -496,11 +535,16 @@ void k_trajectories(TrajArgs a) {
                 }
                 const float rx = signed_unit(ux), ry = signed_unit(uy);
                 steer(dx, dy, gx, gy, R.per, R.Q, R.rnd, rx, ry);
-                const float x1 = x + R.L * dx;
-                const float y1 = y + R.L * dy;
+                x1 = x + R.L * dx;
+                y1 = y + R.L * dy;
+                pl = bilinear_pad_load(dem_rs, Wp, row_bytes, x1, y1);
+            }
+            accumulate();
+            if (alive) {
+                const bool lim = n >= a.S;
                 const float fc1 = floorf(x1), fr1 = floorf(y1);
                 const bool inb = !lim && fc1 >= 0.0f && fc1 < fW && fr1 >= 0.0f && fr1 < fH;
-                const Sample s1 = bilinear_pad(dem_rs, Wp, row_bytes, x1, y1);
+                const Sample s1 = bilinear_pad_value(pl);
                 const float dz = z - s1.z;
                 // dl2 + dz^2 >= dl2: with dl2 >= 2^-96 (a run constant) no lane is below the short form's range
                 const float ds = sqrt_rn(R.dl2 + dz * dz, R.dl2 >= 0x1p-96f);
@@ -546,25 +590,14 @@ void k_trajectories(TrajArgs a) {
                 // 2^23 on an accepted grid and nc is used only for a step inside it
                 const uint32_t nc = R.raster_off + __umul24((uint32_t)(int)fr1, (uint32_t)W) + (uint32_t)(int)fc1;
                 const bool change = acc && nc != cur;
-                leave = change || !acc;
+                leave_key = (change || !acc) ? cur : kEmpty;
                 leave_bits = __float_as_uint(cmax2);
-                leave_key = cur;
                 cur = change ? nc : cur;
                 cmax2 = change ? v2 : ((acc && v2 > cmax2) ? v2 : cmax2);
                 alive = acc;
             }
-            // ---- accumulate the visit that ended: its entry and its largest v^2 (0 bits: nothing to max)
-            if (leave) {
-                const int sl = claim(leave_key);
-                if (sl >= 0) {
-                    atomicAdd(tb.cnt + sl, 1u);
-                    if (leave_bits) atomicMax(tb.vmx + sl, leave_bits);
-                } else {
-                    atomicAdd(counts + leave_key, 1u);
-                    if (leave_bits) global_max(vmax2 + leave_key, leave_bits);
-                }
-            }
         }
+        accumulate();
 
         // ---- epoch boundary: count the waves with work left, flush the table, refill the window
         if (lane == 0 && !finished) atomicAdd(&ctl.busy[epoch & 1u], 1u);
@@ -802,6 +835,8 @@ hipError_t launch_batch_records(const RunSpec* specs, const int32_t* rec_run, co
 
 namespace {
 
+constexpr int kCandidates = 8;  // table slots a key may take: two buckets of four
+
 struct Variant {
     const void* single;
     const void* batch;
@@ -813,21 +848,21 @@ struct Variant {
     void (*launch_batch)(dim3, dim3, hipStream_t, const TrajArgs&);
 };
 
-template <bool B, bool A, int Blk, int F, int T, int Q, int M, int K, int Wpe>
+template <bool B, bool A, int Blk, int F, int T, int M, int K, int Wpe>
 void launch_t(dim3 g, dim3 t, hipStream_t s, const TrajArgs& a) {
-    hipLaunchKernelGGL((k_trajectories<B, A, Blk, F, T, Q, M, K, Wpe>), g, t, 0, s, a);
+    hipLaunchKernelGGL((k_trajectories<B, A, Blk, F, T, M, K, Wpe>), g, t, 0, s, a);
 }
 
-template <int Blk, int F, int T, int Q, int M, int K, int Wpe = 8>
+template <int Blk, int F, int T, int M, int K, int Wpe = 8>
 constexpr Variant make_variant(uint32_t spl = (uint32_t)kSlotsPerLane) {
-    return Variant{reinterpret_cast<const void*>(&k_trajectories<false, true, Blk, F, T, Q, M, K, Wpe>),
-                   reinterpret_cast<const void*>(&k_trajectories<true, true, Blk, F, T, Q, M, K, Wpe>), Blk, spl,
-                   {Blk, F, T, Q, M, K, Wpe},
-                   &launch_t<false, true, Blk, F, T, Q, M, K, Wpe>, &launch_t<false, false, Blk, F, T, Q, M, K, Wpe>,
-                   &launch_t<true, true, Blk, F, T, Q, M, K, Wpe>};
+    return Variant{reinterpret_cast<const void*>(&k_trajectories<false, true, Blk, F, T, M, K, Wpe>),
+                   reinterpret_cast<const void*>(&k_trajectories<true, true, Blk, F, T, M, K, Wpe>), Blk, spl,
+                   {Blk, F, T, kCandidates, M, K, Wpe},
+                   &launch_t<false, true, Blk, F, T, M, K, Wpe>, &launch_t<false, false, Blk, F, T, M, K, Wpe>,
+                   &launch_t<true, true, Blk, F, T, M, K, Wpe>};
 }
 
-// candidates of the autotuner: (threads per block, iterations per epoch, table slots per block, probes,
+// candidates of the autotuner: (threads per block, iterations per epoch, table slots per block,
 // window top-up in blocks of slots, retention threshold[, waves per SIMD of the register budget]) and the
 // slots per lane that size a small problem's grid. 1024-thread blocks run two per CU at eight waves per SIMD
 // (64 VGPRs; 6144 slots of 12 bytes are 72 KiB of LDS per block); the 768- and 512-thread shapes run at six
@@ -838,14 +873,14 @@ constexpr Variant make_variant(uint32_t spl = (uint32_t)kSlotsPerLane) {
 // 0.19 and 0.31 ms), and one that fills it does not see the difference. The first shape is the fastest, or within a
 // few percent of it, on every workload from 10^5 to 2 10^9 steps, so it is also what a call takes that may not time.
 const Variant kVariants[] = {
-    make_variant<512, 16, 4096, 8, 4, 1, 6>(1u),   make_variant<1024, 32, 6144, 4, 4, 2>(),
-    make_variant<1024, 16, 6144, 4, 4, 1>(1u),     make_variant<1024, 32, 6144, 6, 4, 2>(),
-    make_variant<1024, 32, 4096, 4, 4, 0>(),       make_variant<768, 16, 6144, 4, 4, 1, 6>(1u),
-    make_variant<768, 16, 6144, 8, 4, 2, 6>(),     make_variant<512, 16, 4096, 8, 4, 2, 6>(),
-    make_variant<1024, 16, 6144, 4, 4, 1>(2u),     make_variant<1024, 16, 6144, 4, 4, 1>(4u),
-    make_variant<512, 16, 4096, 8, 4, 1, 6>(2u),   make_variant<512, 32, 4096, 8, 4, 2, 6>(),
-    make_variant<512, 16, 4096, 8, 4, 1, 6>(),     make_variant<768, 16, 6144, 4, 4, 1, 6>(),
-    make_variant<384, 16, 3072, 8, 4, 2, 6>(1u),
+    make_variant<512, 16, 4096, 4, 1, 6>(1u),   make_variant<1024, 32, 6144, 4, 2>(),
+    make_variant<1024, 16, 6144, 4, 1>(1u),     make_variant<1024, 16, 6144, 4, 2>(),
+    make_variant<1024, 32, 4096, 4, 0>(),       make_variant<768, 16, 6144, 4, 1, 6>(1u),
+    make_variant<768, 16, 6144, 4, 2, 6>(),     make_variant<512, 16, 4096, 4, 2, 6>(),
+    make_variant<1024, 16, 6144, 4, 1>(2u),     make_variant<1024, 16, 6144, 4, 1>(4u),
+    make_variant<512, 16, 4096, 4, 1, 6>(2u),   make_variant<512, 32, 4096, 4, 2, 6>(),
+    make_variant<512, 16, 4096, 4, 1, 6>(),     make_variant<768, 16, 6144, 4, 1, 6>(),
+    make_variant<384, 16, 3072, 4, 2, 6>(1u),
 };
 
 }  // namespace
@@ -877,7 +912,7 @@ LaunchShape trajectory_shape(bool batched, int variant) {
 }
 
 hipError_t launch_trajectories_record(const TrajArgs& a, hipStream_t s) {
-    auto* k = &k_trajectories<false, true, 1024, 16, 6144, 4, 4, 1, 8, true>;
+    auto* k = &k_trajectories<false, true, 1024, 16, 6144, 4, 1, 8, true>;
     int dev = 0, cus = 256, per_cu = 1;
     if (hipGetDevice(&dev) == hipSuccess &&
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0 &&
