@@ -50,7 +50,7 @@ Workspace carve(void* base, int64_t H, int64_t W, int64_t mult) {
 
 size_t batched_workspace_bytes(int64_t H, int64_t W, int64_t n_tiles, int64_t n_masks, int64_t n_runs) {
     const int64_t n = H * W;
-    return kControl + round256((size_t)scan_blocks(n) * sizeof(uint32_t)) +
+    return kControl + round256((size_t)n_masks * scan_blocks(n) * sizeof(uint32_t)) +
            round256((size_t)n_masks * n * sizeof(int32_t)) + round256((size_t)n_masks * sizeof(int32_t)) +
            round256((size_t)n_runs * sizeof(RunConst)) + round256((size_t)(n_runs + 1) * sizeof(unsigned long long)) +
            round256((size_t)n_runs * 4 * sizeof(unsigned long long)) + round256((size_t)n_masks * sizeof(int32_t)) +
@@ -65,7 +65,7 @@ Workspace carve_batched(void* base, int64_t H, int64_t W, int64_t n_masks, int64
     w.queues = reinterpret_cast<unsigned long long*>(p + 512);
     p += kControl;
     w.blk = reinterpret_cast<uint32_t*>(p);
-    p += round256((size_t)scan_blocks(n) * sizeof(uint32_t));
+    p += round256((size_t)n_masks * scan_blocks(n) * sizeof(uint32_t));
     w.cells = reinterpret_cast<int32_t*>(p);
     p += round256((size_t)n_masks * n * sizeof(int32_t));
     w.n_cells = reinterpret_cast<int32_t*>(p);
@@ -253,10 +253,11 @@ bool capturing(hipStream_t s) {
 // fastest of all variants, each timed once with HIP events after `zero` re-zeroes what the kernel
 // accumulates into. The inputs of the kernel (cell lists, run table) must already be enqueued.
 // may_tune = false: never time the variants here (the allocation-free entry point creates no events); an
-// uncached problem then takes variant 0.
+// uncached problem then takes variant 0. *timed: the variants ran, so what they accumulate into needs clearing again.
 template <class Zero>
 hipError_t choose_variant(const avl::TrajArgs& a, bool batched, const std::vector<int64_t>& key, hipStream_t s,
-                          Zero zero, int* variant, bool may_tune = true) {
+                          Zero zero, int* variant, bool* timed, bool may_tune = true) {
+    *timed = false;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         if (g_variant_override >= 0) {
@@ -273,6 +274,7 @@ hipError_t choose_variant(const avl::TrajArgs& a, bool batched, const std::vecto
         *variant = 0;
         return hipSuccess;
     }
+    *timed = true;
     hipEvent_t e0, e1;
     hipError_t e;
     if ((e = hipEventCreate(&e0)) != hipSuccess) return e;
@@ -319,7 +321,8 @@ hipError_t choose_variant(const avl::TrajArgs& a, bool batched, const std::vecto
 // adjoint). Under capture, or with may_tune false, an uncached key takes variant 0.
 template <class Zero, class Launch>
 hipError_t choose_smooth(const std::vector<int64_t>& key, int nv, hipStream_t s, Zero zero, Launch launch, int* variant,
-                         bool may_tune = true) {
+                         bool* timed, bool may_tune = true) {
+    *timed = false;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         const int32_t forced = g_smooth_override[key[1] == 2 ? 0 : 1];
@@ -337,6 +340,7 @@ hipError_t choose_smooth(const std::vector<int64_t>& key, int nv, hipStream_t s,
         *variant = 0;
         return hipSuccess;
     }
+    *timed = true;
     hipEvent_t e0, e1;
     hipError_t e;
     if ((e = hipEventCreate(&e0)) != hipSuccess) return e;
@@ -607,7 +611,20 @@ int avl_release_cells(const uint8_t* mask, int32_t H, int32_t W, int32_t* cells,
     const int64_t n = (int64_t)H * W;
     if (workspace_bytes < avl::workspace_bytes(H, W)) return fail(AVL_ENOMEM, "avl_release_cells: workspace too small");
     avl::Workspace ws = avl::carve(workspace, H, W);
-    hipError_t e = avl::launch_compact(mask, n, cells, n_cells, ws.blk, static_cast<hipStream_t>(stream));
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    avl::PrepArgs pa{};
+    pa.mask = mask;
+    pa.n = n;
+    pa.n_masks = 1;
+    pa.blk = ws.blk;
+    avl::ListArgs la{};
+    la.mask = mask;
+    la.n = n;
+    la.blk = ws.blk;
+    la.cells = cells;
+    la.n_cells = n_cells;
+    hipError_t e = avl::launch_prepare(pa, s);
+    if (e == hipSuccess) e = avl::launch_release_list(la, 1, s);
     return e == hipSuccess ? AVL_OK : hip_fail(e, "avl_release_cells");
 }
 
@@ -703,24 +720,48 @@ int single_pass(const char* where, const float* dem, const uint8_t* mask, int32_
     a.runout_angle = params->tan_alpha >= 0.0f ? 1u : 0u;
     a.wdiv = avl::make_divu32((uint32_t)W);
 
-    auto zero = [&]() -> hipError_t {
-        hipError_t e;
-        if ((e = avl::launch_fill_u32(counts, 0u, n, s)) != hipSuccess) return e;
-        if ((e = avl::launch_fill_u32(a.vmax2, 0u, n, s)) != hipSuccess) return e;
-        if ((e = avl::launch_fill_u64(ws.queues, 0ull, avl::kXcds * avl::kQueueStride, s)) != hipSuccess) return e;
-        return avl::launch_fill_u64(a.stats, 0ull, 4, s);
-    };
+    // everything that depends on the inputs alone in one launch, then the release cells, their start records and the run
+    // table in another (and a scan of the counts before it for a large mask)
+    avl::PrepArgs clear{};
+    clear.fill[0] = {counts, n, 0u};
+    clear.fill[1] = {a.vmax2, n, 0u};
+    clear.fill[2] = {reinterpret_cast<uint32_t*>(ws.queues), 2 * avl::kXcds * (int64_t)avl::kQueueStride, 0u};
+    clear.fill[3] = {reinterpret_cast<uint32_t*>(a.stats), 8, 0u};
+    auto zero = [&]() -> hipError_t { return avl::launch_prepare(clear, s); };
+    avl::PrepArgs pa = clear;
+    pa.dem = dem;
+    pa.dem_pad = ws.dem_pad;
+    pa.H = H;
+    pa.W = W;
+    pa.n_tiles = 1;
+    pa.mask = mask;
+    pa.n = nf;
+    pa.n_masks = 1;
+    pa.blk = ws.blk;
+    if (rec) pa.fill[4] = {rec->ends, (int64_t)rec->n, ~0u};
+    avl::ListArgs la{};
+    la.mask = mask;
+    la.n = nf;
+    la.blk = ws.blk;
+    la.cells = ws.cells;
+    la.n_cells = ws.n_cells;
+    la.dem = dem;
+    la.H = H;
+    la.W = W;
+    la.mult = (uint32_t)mult;
+    la.starts = ws.starts;
+    la.cap = nf;
+    la.setup.spec = {0u, 0u, 0u, run_id, (unsigned long long)seed};
+    la.setup.p = *params;
+    la.setup.cs = cell_size;
+    la.setup.P = particles_per_cell;
+    la.setup.run = ws.runs;
+    la.setup.run_off = ws.run_off;
+    la.setup.cap_cells = -1;
     hipError_t e;
-    if ((e = avl::launch_compact(mask, nf, ws.cells, ws.n_cells, ws.blk, s)) != hipSuccess)
-        return hip_fail(e, (std::string(where) + ": compaction").c_str());
-    if ((e = avl::launch_start_records(dem, H, W, mult, ws.cells, ws.n_cells, nf, ws.starts, s)) != hipSuccess)
-        return hip_fail(e, (std::string(where) + ": start records").c_str());
-    if ((e = avl::launch_pad_dem(dem, H, W, ws.dem_pad, s)) != hipSuccess)
-        return hip_fail(e, (std::string(where) + ": padded DEM").c_str());
-    const avl::RunSpec spec{0u, 0u, 0u, run_id, (unsigned long long)seed};
-    if ((e = avl::launch_setup_runs(nullptr, nullptr, 0, spec, *params, ws.n_cells, 1, 1, 1, H, W, cell_size,
-                                    particles_per_cell, false, ws.runs, ws.run_off, nullptr, s)) != hipSuccess)
-        return hip_fail(e, (std::string(where) + ": run setup").c_str());
+    if ((e = avl::launch_prepare(pa, s)) != hipSuccess) return hip_fail(e, (std::string(where) + ": prepare").c_str());
+    if ((e = avl::launch_release_list(la, 1, s)) != hipSuccess)
+        return hip_fail(e, (std::string(where) + ": release cells").c_str());
     if (rec) {
         a.rec_first = rec->first;
         a.rec_n = rec->n;
@@ -729,8 +770,6 @@ int single_pass(const char* where, const float* dem, const uint8_t* mask, int32_
         a.rec_xy = reinterpret_cast<float2*>(rec->points);
         a.rec_v2 = rec->speeds2;
         a.rec_end = rec->ends;
-        if ((e = zero()) != hipSuccess || (e = avl::launch_fill_u32(rec->ends, ~0u, rec->n, s)) != hipSuccess)
-            return hip_fail(e, (std::string(where) + ": zero").c_str());
         if ((e = timed(s, [&] { return avl::launch_trajectories_record(a, s); })) != hipSuccess)
             return hip_fail(e, (std::string(where) + ": launch").c_str());
         if ((e = avl::launch_finalize_vmax(a.vmax2, n, s)) != hipSuccess)
@@ -738,11 +777,12 @@ int single_pass(const char* where, const float* dem, const uint8_t* mask, int32_
         return AVL_OK;
     }
     int variant = 0;
-    if ((e = choose_variant(a, false, tune_key(false, nf, 1, particles_per_cell, step_limit), s, zero, &variant,
+    bool tuned = false;
+    if ((e = choose_variant(a, false, tune_key(false, nf, 1, particles_per_cell, step_limit), s, zero, &variant, &tuned,
                             !noalloc)) != hipSuccess)
         return hip_fail(e, (std::string(where) + ": autotune").c_str());
     g_last_variant = variant;
-    if ((e = zero()) != hipSuccess) return hip_fail(e, (std::string(where) + ": zero").c_str());
+    if (tuned && (e = zero()) != hipSuccess) return hip_fail(e, (std::string(where) + ": zero").c_str());
     if ((e = timed_launch(a, false, avl::trajectory_shape(false, variant), s)) != hipSuccess)
         return hip_fail(e, (std::string(where) + ": launch").c_str());
     if ((e = avl::launch_finalize_vmax(a.vmax2, n, s)) != hipSuccess)
@@ -821,9 +861,14 @@ int avl_bench_gather(const float* dem, int32_t H, int32_t W, const uint32_t* gat
     hipStream_t s = static_cast<hipStream_t>(stream);
     avl::Workspace ws = avl::carve(workspace, H, W);
     hipError_t e;
-    if ((e = avl::launch_pad_dem(dem, H, W, ws.dem_pad, s)) != hipSuccess ||
-        (e = avl::launch_fill_u32(checksum, 0u, 1, s)) != hipSuccess)
-        return hip_fail(e, "avl_bench_gather: set-up");
+    avl::PrepArgs pa{};
+    pa.dem = dem;
+    pa.dem_pad = ws.dem_pad;
+    pa.H = H;
+    pa.W = W;
+    pa.n_tiles = 1;
+    pa.fill[0] = {checksum, 1, 0u};
+    if ((e = avl::launch_prepare(pa, s)) != hipSuccess) return hip_fail(e, "avl_bench_gather: set-up");
     if (n_gathers == 0) return AVL_OK;
     const uint32_t pad_bytes = (uint32_t)(avl::padded_cells(H, W) * sizeof(float));
     e = timed(s, [&] {
@@ -841,9 +886,10 @@ int avl_bench_atomics(int32_t H, int32_t W, const uint32_t* visits, uint64_t n_v
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int64_t n = (int64_t)H * W;
     hipError_t e;
-    if ((e = avl::launch_fill_u32(counts, 0u, n, s)) != hipSuccess ||
-        (e = avl::launch_fill_u32(vmax2_bits, 0u, n, s)) != hipSuccess)
-        return hip_fail(e, "avl_bench_atomics: set-up");
+    avl::PrepArgs pa{};
+    pa.fill[0] = {counts, n, 0u};
+    pa.fill[1] = {vmax2_bits, n, 0u};
+    if ((e = avl::launch_prepare(pa, s)) != hipSuccess) return hip_fail(e, "avl_bench_atomics: set-up");
     if (n_visits == 0) return AVL_OK;
     e = timed(s, [&] {
         return avl::launch_replay_atomics(reinterpret_cast<const uint2*>(visits), n_visits, counts, vmax2_bits, s);
@@ -1016,41 +1062,68 @@ int smooth_forward(const float* dem, const uint8_t* mask, const float* mass, int
     a.vel_q = vel ? reinterpret_cast<unsigned long long*>(velocity_q) : nullptr;
     a.stats = stats ? reinterpret_cast<unsigned long long*>(stats) : sw.w.stats;
     hipError_t e;
-    if (!prepared && (e = avl::launch_compact(mask, n, sw.w.cells, sw.w.n_cells, sw.w.blk, s)) != hipSuccess)
-        return hip_fail(e, "avl_trajectories_smooth: compaction");
-    const avl::RunSpec spec{0u, 0u, 0u, run_id, (unsigned long long)seed};
-    if ((e = avl::launch_setup_runs(p_dev ? spec_dev : nullptr, p_dev, p_dev ? 1u : 0u, spec, *params, sw.w.n_cells,
-                                    1, 1, 1, H, W, cell_size, particles_per_cell, false, sw.w.runs, sw.w.run_off,
-                                    status, s, max_release_cells)) != hipSuccess)
-        return hip_fail(e, "avl_trajectories_smooth: run setup");
-    auto zero = [&]() -> hipError_t {
-        hipError_t z;
-        if ((z = avl::launch_fill_u32(reinterpret_cast<uint32_t*>(deposit_q), 0u, 2 * n, s)) != hipSuccess) return z;
-        if (vel && (z = avl::launch_fill_u32(reinterpret_cast<uint32_t*>(velocity_q), 0u, 2 * n, s)) != hipSuccess)
-            return z;
-        if ((z = avl::launch_fill_u64(sw.w.queues, 0ull, avl::kXcds * avl::kQueueStride, s)) != hipSuccess) return z;
-        return avl::launch_fill_u64(a.stats, 0ull, 4, s);
-    };
-    if (!prepared && (e = avl::launch_pad_dem(dem, H, W, sw.dem_pad, s)) != hipSuccess)
-        return hip_fail(e, "avl_trajectories_smooth: padded DEM");
-    if (!prepared &&
-        ((e = avl::launch_start_records(dem, H, W, 1, sw.w.cells, sw.w.n_cells, max_release_cells, sw.starts, s)) !=
-             hipSuccess ||
-         (e = avl::launch_particle_mass(mass, sw.w.cells, sw.w.n_cells, max_release_cells, particles_per_cell,
-                                        sw.mpc, s)) != hipSuccess))
-        return hip_fail(e, "avl_trajectories_smooth: start records");
+    avl::PrepArgs clear{};
+    clear.fill[0] = {reinterpret_cast<uint32_t*>(deposit_q), 2 * n, 0u};
+    if (vel) clear.fill[1] = {reinterpret_cast<uint32_t*>(velocity_q), 2 * n, 0u};
+    clear.fill[2] = {reinterpret_cast<uint32_t*>(sw.w.queues), 2 * avl::kXcds * (int64_t)avl::kQueueStride, 0u};
+    clear.fill[3] = {reinterpret_cast<uint32_t*>(a.stats), 8, 0u};
+    auto zero = [&]() -> hipError_t { return avl::launch_prepare(clear, s); };
+    avl::SetupOne su{};
+    su.spec_dev = p_dev ? spec_dev : nullptr;
+    su.p_dev = p_dev;
+    su.spec = {0u, 0u, 0u, run_id, (unsigned long long)seed};
+    su.p = *params;
+    su.cs = cell_size;
+    su.P = particles_per_cell;
+    su.run = sw.w.runs;
+    su.run_off = sw.w.run_off;
+    su.status = status;
+    su.cap_cells = max_release_cells;
+    if (prepared) {
+        if ((e = avl::launch_setup_one(su, H, W, sw.w.n_cells, s)) != hipSuccess)
+            return hip_fail(e, "avl_trajectories_smooth: run setup");
+        if ((e = zero()) != hipSuccess) return hip_fail(e, "avl_trajectories_smooth: zero");
+    } else {
+        avl::PrepArgs pa = clear;
+        pa.dem = dem;
+        pa.dem_pad = sw.dem_pad;
+        pa.H = H;
+        pa.W = W;
+        pa.n_tiles = 1;
+        pa.mask = mask;
+        pa.n = n;
+        pa.n_masks = 1;
+        pa.blk = sw.w.blk;
+        avl::ListArgs la{};
+        la.mask = mask;
+        la.n = n;
+        la.blk = sw.w.blk;
+        la.cells = sw.w.cells;
+        la.n_cells = sw.w.n_cells;
+        la.dem = dem;
+        la.H = H;
+        la.W = W;
+        la.mult = 1;
+        la.starts = sw.starts;
+        la.cap = max_release_cells;
+        la.mass = mass;
+        la.mpc = sw.mpc;
+        la.setup = su;
+        if ((e = avl::launch_prepare(pa, s)) != hipSuccess) return hip_fail(e, "avl_trajectories_smooth: prepare");
+        if ((e = avl::launch_release_list(la, 1, s)) != hipSuccess)
+            return hip_fail(e, "avl_trajectories_smooth: release cells");
+    }
     int variant = 0;
+    bool tuned = false;
     if ((e = choose_smooth(smooth_key(2, n, max_release_cells, particles_per_cell, step_limit),
                            avl::smooth_forward_variants(), s, zero,
-                           [&](int v) { return avl::launch_smooth_forward(a, v, s); }, &variant)) != hipSuccess)
+                           [&](int v) { return avl::launch_smooth_forward(a, v, s); }, &variant, &tuned)) != hipSuccess)
         return hip_fail(e, "avl_trajectories_smooth: autotune");
-    if ((e = zero()) != hipSuccess) return hip_fail(e, "avl_trajectories_smooth: zero");
+    if (tuned && (e = zero()) != hipSuccess) return hip_fail(e, "avl_trajectories_smooth: zero");
     if ((e = avl::launch_smooth_forward(a, variant, s)) != hipSuccess)
         return hip_fail(e, "avl_trajectories_smooth: launch");
-    if (deposit && (e = avl::launch_q_to_float(a.dep_q, n, deposit, s)) != hipSuccess)
-        return hip_fail(e, "avl_trajectories_smooth: deposit");
-    if (vel && velocity && (e = avl::launch_q_to_float(a.vel_q, n, velocity, s)) != hipSuccess)
-        return hip_fail(e, "avl_trajectories_smooth: velocity");
+    if ((e = avl::launch_q_to_float(a.dep_q, deposit, vel && velocity ? a.vel_q : nullptr, velocity, n, s)) != hipSuccess)
+        return hip_fail(e, "avl_trajectories_smooth: rasters");
     return AVL_OK;
 }
 }  // namespace
@@ -1087,15 +1160,15 @@ int smooth_backward(const float* dem, const uint8_t* mask, const float* mass, in
     a.gD = grad_deposit;
     a.pdev = p_dev;
     hipError_t e;
-    auto zero = [&]() -> hipError_t {
-        hipError_t z;
-        if ((z = avl::launch_fill_u32(reinterpret_cast<uint32_t*>(dmass), 0u, n, s)) != hipSuccess) return z;
-        return avl::launch_fill_u64(sw.w.queues, 0ull, avl::kXcds * avl::kQueueStride, s);
-    };
+    avl::PrepArgs clear{};
+    clear.fill[0] = {reinterpret_cast<uint32_t*>(dmass), n, 0u};
+    clear.fill[1] = {reinterpret_cast<uint32_t*>(sw.w.queues), 2 * avl::kXcds * (int64_t)avl::kQueueStride, 0u};
+    auto zero = [&]() -> hipError_t { return avl::launch_prepare(clear, s); };
     int variant = 0;
+    bool tuned = false;
     if ((e = choose_smooth(smooth_key(3, n, max_release_cells, particles_per_cell, step_limit),
                            avl::smooth_backward_variants(), s, zero,
-                           [&](int v) { return avl::launch_smooth_backward_kernel(a, v, s); }, &variant)) !=
+                           [&](int v) { return avl::launch_smooth_backward_kernel(a, v, s); }, &variant, &tuned)) !=
         hipSuccess)
         return hip_fail(e, "avl_trajectories_backward: autotune");
     if ((e = zero()) != hipSuccess) return hip_fail(e, "avl_trajectories_backward: zero");
@@ -1173,31 +1246,40 @@ int avl_trajectories_batched(const float* dems, int32_t n_tiles, const uint8_t* 
     a.pad_bytes = (uint32_t)(np * sizeof(float));
     const int64_t raster = (int64_t)n_runs * n;
 
-    auto zero = [&]() -> hipError_t {
-        hipError_t e;
-        if ((e = avl::launch_fill_u32(counts, 0u, raster, s)) != hipSuccess) return e;
-        if ((e = avl::launch_fill_u32(a.vmax2, 0u, raster, s)) != hipSuccess) return e;
-        if ((e = avl::launch_fill_u64(ws.queues, 0ull, avl::kXcds * avl::kQueueStride, s)) != hipSuccess) return e;
-        return avl::launch_fill_u64(a.stats, 0ull, 4 * (int64_t)n_runs, s);
-    };
-    // padded copies of the tiles, release-cell lists of every scenario, then the run table
+    avl::PrepArgs clear{};
+    clear.fill[0] = {counts, raster, 0u};
+    clear.fill[1] = {a.vmax2, raster, 0u};
+    clear.fill[2] = {reinterpret_cast<uint32_t*>(ws.queues), 2 * avl::kXcds * (int64_t)avl::kQueueStride, 0u};
+    clear.fill[3] = {reinterpret_cast<uint32_t*>(a.stats), 8 * (int64_t)n_runs, 0u};
+    auto zero = [&]() -> hipError_t { return avl::launch_prepare(clear, s); };
+    // cleared rasters and counters, padded copies of the tiles and mask counts, the release-cell list of every scenario,
+    // then the run table and the start records
     auto prologue = [&]() -> hipError_t {
         hipError_t e;
-        for (int32_t t = 0; t < n_tiles; ++t)
-            if ((e = avl::launch_pad_dem(dems + (size_t)t * n, H, W, ws.dem_pad + (size_t)t * np, s)) != hipSuccess)
-                return e;
-        for (int32_t m = 0; m < n_masks; ++m)
-            if ((e = avl::launch_compact(masks + (size_t)m * n, n, ws.cells + (size_t)m * n, ws.n_cells + m, ws.blk,
-                                         s)) != hipSuccess)
-                return e;
-        const avl::RunSpec none{};
-        const avl_params none_p{};
-        if ((e = avl::launch_fill_u32(reinterpret_cast<uint32_t*>(ws.rec_run), 0x7FFFFFFFu, n_masks, s)) != hipSuccess)
-            return e;
-        if ((e = avl::launch_setup_runs(reinterpret_cast<const avl::RunSpec*>(runs), params, (uint32_t)n_params, none,
-                                        none_p, ws.n_cells, (uint32_t)n_masks, (uint32_t)n_tiles, (uint32_t)n_runs, H,
-                                        W, cell_size, particles_per_cell, true, ws.runs, ws.run_off, run_status, s, -1,
-                                        ws.rec_run)) != hipSuccess)
+        avl::PrepArgs pa = clear;
+        pa.fill[4] = {reinterpret_cast<uint32_t*>(ws.rec_run), n_masks, 0x7FFFFFFFu};
+        pa.dem = dems;
+        pa.dem_pad = ws.dem_pad;
+        pa.H = H;
+        pa.W = W;
+        pa.n_tiles = (uint32_t)n_tiles;
+        pa.mask = masks;
+        pa.n = n;
+        pa.n_masks = (uint32_t)n_masks;
+        pa.blk = ws.blk;
+        if ((e = avl::launch_prepare(pa, s)) != hipSuccess) return e;
+        avl::ListArgs la{};
+        la.mask = masks;
+        la.n = n;
+        la.blk = ws.blk;
+        la.cells = ws.cells;
+        la.cells_stride = n;
+        la.n_cells = ws.n_cells;
+        if ((e = avl::launch_release_list(la, (uint32_t)n_masks, s)) != hipSuccess) return e;
+        if ((e = avl::launch_setup_runs(reinterpret_cast<const avl::RunSpec*>(runs), params, (uint32_t)n_params,
+                                        ws.n_cells, (uint32_t)n_masks, (uint32_t)n_tiles, (uint32_t)n_runs, H, W,
+                                        cell_size, particles_per_cell, ws.runs, ws.run_off, run_status, ws.rec_run,
+                                        s)) != hipSuccess)
             return e;
         return avl::launch_batch_records(reinterpret_cast<const avl::RunSpec*>(runs), ws.rec_run, ws.n_cells,
                                          (uint32_t)n_masks, ws.cells, ws.dem_pad, H, W, ws.starts, s);
@@ -1205,7 +1287,6 @@ int avl_trajectories_batched(const float* dems, int32_t n_tiles, const uint8_t* 
     auto body = [&](const avl::LaunchShape& shape) -> hipError_t {
         hipError_t e;
         if ((e = prologue()) != hipSuccess) return e;
-        if ((e = zero()) != hipSuccess) return e;
         if ((e = timed_launch(a, true, shape, s)) != hipSuccess) return e;
         return avl::launch_finalize_vmax(a.vmax2, raster, s);
     };
@@ -1222,7 +1303,8 @@ int avl_trajectories_batched(const float* dems, int32_t n_tiles, const uint8_t* 
     if (!known && !capturing(s)) {
         if ((e = prologue()) != hipSuccess) return hip_fail(e, "avl_trajectories_batched: setup");
     }
-    if ((e = choose_variant(a, true, tkey, s, zero, &variant)) != hipSuccess)
+    bool tuned = false;  // the body clears again in any case
+    if ((e = choose_variant(a, true, tkey, s, zero, &variant, &tuned)) != hipSuccess)
         return hip_fail(e, "avl_trajectories_batched: autotune");
     g_last_variant = variant;
     const avl::LaunchShape shape = avl::trajectory_shape(true, variant);  // queried outside any capture

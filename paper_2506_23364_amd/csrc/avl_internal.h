@@ -22,7 +22,7 @@ constexpr int kWave = 64;
 //                many) and the padded DEM (f32, (H + 2) x (W + 2))
 // Batch (avl_batched_workspace_bytes):
 //   [0, kControl) control block: per-XCD slot queues @512, kQueueStride words apart
-//   then         compaction scan sums; n_masks release-cell lists (i32, H*W each); n_masks cell counts;
+//   then         compaction scan sums per mask; n_masks release-cell lists (i32, H*W each); n_masks cell counts;
 //                n_runs RunConst; n_runs + 1 slot offsets; n_runs x 4 internal statistics; n_tiles padded
 //                DEM tiles (f32, (H + 2) x (W + 2) each)
 // Every region starts on a 256-byte boundary.
@@ -64,7 +64,7 @@ Workspace carve_batched(void* base, int64_t H, int64_t W, int64_t n_masks, int64
 
 // ------------------------------------------------------------------ trajectory kernel arguments
 // Derived constants of one run (one parameter set on one DEM tile and release scenario), binary32,
-// computed on the device by k_setup_runs in the model's order.
+// computed on the device (prepare.hip) in the model's order.
 struct RunConst {
     float per, Q, rnd, L;      // persistence, 1 - persistence, randomness, step length (cells)
     float dl2, mdl, cd, tca;   // (L cs)^2, mu L cs, 2g / (xi h), tan(alpha) cs
@@ -157,8 +157,6 @@ hipError_t launch_snow_cover(const float* normals4, const float* dem, int64_t n,
                              float c_hi, float* alpha, hipStream_t s);
 hipError_t launch_release_mask_fine(const float* normals4, const float* dem, int H, int W, int mult, float cmin,
                                     float cmax, float zmin, float zmax, uint8_t* mask, hipStream_t s);
-hipError_t launch_compact(const uint8_t* mask, int64_t n, int32_t* cells, int32_t* n_cells, uint32_t* blk,
-                          hipStream_t s);
 // Overlay mipmap: up to kMipPass output levels per pass (a 32 x 32 tile of the first halves to 1 x 1).
 constexpr int kMipPass = 6;
 struct MipLevels {
@@ -168,28 +166,80 @@ struct MipLevels {
 };
 hipError_t launch_mip_pass(const void* cin, bool cin64, const float* vin, int h0, int w0, int nlev,
                            const MipLevels& o, hipStream_t s);
-hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s);
-hipError_t launch_fill_u64(unsigned long long* p, unsigned long long v, int64_t n, hipStream_t s);
-// (H + 2) x (W + 2) copy of the DEM with the edge texels replicated into a one-texel border.
-hipError_t launch_pad_dem(const float* dem, int H, int W, float* out, hipStream_t s);
-// starts[i] for each of the first min(*n_cells, n) release cells (the records array holds n).
-hipError_t launch_start_records(const float* dem, int H, int W, int mult, const int32_t* cells,
-                                const int32_t* n_cells, int64_t n, StartRec* starts, hipStream_t s);
-// Setup of the run table: per run, constants from its parameter set and the slot count from its
-// scenario's release-cell count (written by the compaction); then 64-aligned slot offsets.
+
+// ------------------------------------------------------------------ before the particles (prepare.hip)
 struct RunSpec {
     uint32_t tile, scenario, param, run_id;
     unsigned long long seed;
 };
-// specs/params: device arrays (batched) or NULL, then one_spec/one_param are used for the single run.
-// cap_cells >= 0: a run whose scenario has more release cells than cap_cells gets no slots (status 3).
-// rec_run (batched, n_scen entries filled with INT32_MAX beforehand, or NULL): receives per scenario the
-// lowest valid run index that uses it; a run whose tile is that run's tile gets use_rec = 1.
-hipError_t launch_setup_runs(const RunSpec* specs, const ::avl_params* params, uint32_t n_params, RunSpec one_spec,
-                             ::avl_params one_param, const int32_t* n_cells_per_scen, uint32_t n_scen, uint32_t n_tiles,
-                             uint32_t n_runs, int32_t H, int32_t W, float cell_size, uint32_t P, bool batched,
-                             RunConst* runs, unsigned long long* run_off, int32_t* status, hipStream_t s,
-                             int64_t cap_cells = -1, int32_t* rec_run = nullptr);
+struct Fill {
+    uint32_t* p;  // null: none
+    int64_t n;    // words
+    uint32_t v;
+};
+constexpr int kFills = 6;
+// One launch: fills, padded copies of the DEM tiles (dem null: none; (H + 2) x (W + 2) each, edge texels replicated
+// into a one-texel border) and the counts of nonzero bytes per kScanChunk texels of each mask (mask null: none).
+struct PrepArgs {
+    Fill fill[kFills];
+    const float* dem;
+    float* dem_pad;
+    int32_t H, W;
+    uint32_t n_tiles;
+    const uint8_t* mask;
+    int64_t n;  // texels of a mask
+    uint32_t n_masks;
+    uint32_t* blk;  // n_masks x scan_blocks(n)
+    // set by the launcher
+    uint32_t nb, count_blocks, pad_nb, pad_blocks, fill_blocks[kFills];
+    DivU32 wpdiv;
+};
+hipError_t launch_prepare(PrepArgs a, hipStream_t s);
+// The run table of a single run, from host values or (a loop that updates the parameters on the device) device copies.
+// cap_cells >= 0: a mask with more release cells than that gets no slots (status 3).
+struct SetupOne {
+    const RunSpec* spec_dev;      // nullable
+    const ::avl_params* p_dev;    // nullable
+    RunSpec spec;
+    ::avl_params p;
+    float cs;
+    uint32_t P;
+    RunConst* run;                // null: no run table
+    unsigned long long* run_off;  // 2
+    int32_t* status;              // nullable
+    int64_t cap_cells;
+};
+hipError_t launch_setup_one(const SetupOne& u, int H, int W, const int32_t* n_cells, hipStream_t s);
+// Per mask the row-major list of its nonzero texels behind launch_prepare's counts, and their number into n_cells. With
+// starts (one mask): the start record of each of the first cap, with mpc also the mass each of its particles carries
+// (mass null: 1 per texel). With setup.run: the single run's table.
+struct ListArgs {
+    const uint8_t* mask;
+    int64_t n;
+    uint32_t* blk;
+    int32_t* cells;
+    int64_t cells_stride;  // entries between the lists of consecutive masks
+    int32_t* n_cells;
+    const float* dem;
+    int32_t H, W;
+    uint32_t mult;  // release texels per DEM cell edge
+    StartRec* starts;
+    int64_t cap;
+    const float* mass;
+    float* mpc;
+    SetupOne setup;
+    // set by the launcher
+    uint32_t nb;
+    int32_t scanned;
+};
+hipError_t launch_release_list(ListArgs a, uint32_t n_masks, hipStream_t s);
+// Run table of a batch: per run, constants from its parameter set and the slot count from its scenario's release-cell
+// count; then 64-aligned slot offsets. rec_run (n_scen entries filled with INT32_MAX beforehand) receives per scenario
+// the lowest valid run index that uses it; a run whose tile is that run's tile gets use_rec = 1.
+hipError_t launch_setup_runs(const RunSpec* specs, const ::avl_params* params, uint32_t n_params,
+                             const int32_t* n_cells_per_scen, uint32_t n_scen, uint32_t n_tiles, uint32_t n_runs,
+                             int32_t H, int32_t W, float cell_size, uint32_t P, RunConst* runs,
+                             unsigned long long* run_off, int32_t* status, int32_t* rec_run, hipStream_t s);
 // Batch: start records of every scenario's release cells on the tile of the scenario's first valid run
 // (rec_run from the run setup), read from the padded tiles; starts and cells are n_scen x HW arrays.
 hipError_t launch_batch_records(const RunSpec* specs, const int32_t* rec_run, const int32_t* n_cells_per_scen,
@@ -252,10 +302,9 @@ hipError_t launch_smooth_backward_kernel(const SmoothArgs& a, int variant, hipSt
 // the adjoint's reductions after its kernel: dL/dparams and dL/dmass
 hipError_t launch_smooth_reductions(const SmoothArgs& a, const int32_t* n_cells, float* dmass, int64_t n_grid,
                                     double* part, double* dparams, hipStream_t s);
-hipError_t launch_q_to_float(const unsigned long long* q, int64_t n, float* out, hipStream_t s);
-// per release cell i < *n_cells: mpc[i] = (mass ? mass[cells[i]] : 1) / P, the mass each of its particles carries
-hipError_t launch_particle_mass(const float* mass, const int32_t* cells, const int32_t* n_cells, int64_t cap,
-                                uint32_t P, float* mpc, hipStream_t s);
+// q0 -> out0 and q1 -> out1 (either pair may be null)
+hipError_t launch_q_to_float(const unsigned long long* q0, float* out0, const unsigned long long* q1, float* out1, int64_t n,
+                             hipStream_t s);
 // calibration loss: gD = c (D - T) and L = sum (D - T)^2 / N (binary64, fixed order) into *loss
 hipError_t launch_mse_grad(const float* dep, const float* target, int64_t n, float c, float* gD, double* part,
                            double* loss, hipStream_t s);

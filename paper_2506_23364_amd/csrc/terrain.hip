@@ -1,7 +1,6 @@
 // Terrain passes of the avalanche overlay (section 5.2 of arXiv 2506.23364): surface normals and
-// steepness per DEM texel, the release-point map from a steepness range and an elevation window, and
-// the row-major list of release texels. Plus the fill, padded-DEM and finalize helpers of the trajectory
-// pass.
+// steepness per DEM texel, the release-point map from a steepness range and an elevation window. Plus the
+// finalize pass of the trajectory pass and the overlay mipmap.
 //
 // These are streaming passes, written for 64-wide wavefronts with every wave touching whole 256-byte
 // stretches of consecutive cells; all but the normals (bound by their correctly rounded arithmetic) are
@@ -258,162 +257,14 @@ hipError_t launch_release_mask_fine(const float* normals4, const float* dem, int
     return hipGetLastError();
 }
 
-// ------------------------------------------------------------------------------------------ compaction
-// Order-preserving stream compaction of the mask into linear indices, in three passes over
-// kScanChunk-cell blocks: per-block counts, one-block exclusive scan of the counts, per-block write.
-
-__device__ inline uint32_t wave_incl_scan(uint32_t v) {
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        uint32_t t = __shfl_up(v, d, kWave);
-        if (lane >= d) v += t;
-    }
-    return v;
-}
-
-// exclusive scan of one value per thread over a block of kScanThreads; returns the block total in *total
-__device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t* total) {
-    __shared__ uint32_t wsum[kScanThreads / kWave];
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    const uint32_t inc = wave_incl_scan(v);
-    if (lane == kWave - 1) wsum[wid] = inc;
-    __syncthreads();
-    uint32_t before = 0, tot = 0;
-#pragma unroll
-    for (int k = 0; k < kScanThreads / kWave; ++k) {
-        before += (k < wid) ? wsum[k] : 0u;
-        tot += wsum[k];
-    }
-    __syncthreads();
-    *total = tot;
-    return before + inc - v;
-}
-
-// the 16 mask bytes of a thread, [base, base + 16): one 16-byte load when all of them are in range and the
-// address is 16-byte aligned (a lane per 16 bytes, so a wave reads 1 KiB contiguously), else byte by byte with
-// the bytes past n read as 0
-__device__ inline uint4 mask16(const uint8_t* __restrict__ mask, int64_t base, int64_t n) {
-    static_assert(kScanPerThread == 16, "one 16-byte load per thread");
-    if (base + 16 <= n && (reinterpret_cast<uintptr_t>(mask + base) & 15) == 0)
-        return *reinterpret_cast<const uint4*>(mask + base);
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-    for (int k = 0; k < 16; ++k)
-        if (base + k < n) w[k >> 2] |= (uint32_t)mask[base + k] << (8 * (k & 3));
-    return make_uint4(w[0], w[1], w[2], w[3]);
-}
-
-// bit 7 of each byte of the result is set iff that byte of w is nonzero
-__device__ inline uint32_t nonzero_bytes(uint32_t w) {
-    return (((w & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | w) & 0x80808080u;
-}
-
-__device__ inline uint32_t count16(const uint4 m) {
-    return __popc(nonzero_bytes(m.x)) + __popc(nonzero_bytes(m.y)) + __popc(nonzero_bytes(m.z)) +
-           __popc(nonzero_bytes(m.w));
-}
-
-__global__ __launch_bounds__(kScanThreads) void k_compact_count(const uint8_t* __restrict__ mask, int64_t n,
-                                                                uint32_t* __restrict__ blk) {
-    const int64_t base = (int64_t)blockIdx.x * kScanChunk + (int64_t)threadIdx.x * kScanPerThread;
-    uint32_t total;
-    (void)block_excl_scan(count16(mask16(mask, base, n)), &total);
-    if (threadIdx.x == 0) blk[blockIdx.x] = total;
-}
-
-// one block: exclusive scan of nb block counts in place; the grand total goes to *n_cells
-__global__ __launch_bounds__(1024) void k_compact_scan(uint32_t* __restrict__ blk, int64_t nb,
-                                                       int32_t* __restrict__ n_cells) {
-    __shared__ uint32_t wsum[1024 / kWave];
-    const int64_t per = (nb + 1023) / 1024;
-    const int64_t b0 = (int64_t)threadIdx.x * per;
-    uint32_t local = 0;
-    for (int64_t k = 0; k < per; ++k)
-        if (b0 + k < nb) local += blk[b0 + k];
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    const uint32_t inc = wave_incl_scan(local);
-    if (lane == kWave - 1) wsum[wid] = inc;
-    __syncthreads();
-    uint32_t before = 0, tot = 0;
-    for (int k = 0; k < 1024 / kWave; ++k) {
-        before += (k < wid) ? wsum[k] : 0u;
-        tot += wsum[k];
-    }
-    uint32_t run = before + inc - local;
-    for (int64_t k = 0; k < per; ++k) {
-        if (b0 + k < nb) {
-            const uint32_t v = blk[b0 + k];
-            blk[b0 + k] = run;
-            run += v;
-        }
-    }
-    if (threadIdx.x == 0) *n_cells = (int32_t)tot;
-}
-
-__global__ __launch_bounds__(kScanThreads) void k_compact_write(const uint8_t* __restrict__ mask, int64_t n,
-                                                                const uint32_t* __restrict__ blk,
-                                                                int32_t* __restrict__ cells) {
-    const int64_t base = (int64_t)blockIdx.x * kScanChunk + (int64_t)threadIdx.x * kScanPerThread;
-    uint32_t total;
-    const uint4 m = mask16(mask, base, n);
-    uint32_t pos = blk[blockIdx.x] + block_excl_scan(count16(m), &total);
-    const uint32_t w[4] = {nonzero_bytes(m.x), nonzero_bytes(m.y), nonzero_bytes(m.z), nonzero_bytes(m.w)};
-#pragma unroll
-    for (int k = 0; k < kScanPerThread; ++k)  // bytes past n were read as 0
-        if ((w[k >> 2] >> (8 * (k & 3) + 7)) & 1u) cells[pos++] = (int32_t)(base + k);
-}
-
-hipError_t launch_compact(const uint8_t* mask, int64_t n, int32_t* cells, int32_t* n_cells, uint32_t* blk,
-                          hipStream_t s) {
-    const int64_t nb = scan_blocks(n);
-    if (nb == 0) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_compact_count, dim3((unsigned)nb), dim3(kScanThreads), 0, s, mask, n, blk);
-    hipLaunchKernelGGL(k_compact_scan, dim3(1), dim3(1024), 0, s, blk, nb, n_cells);
-    hipLaunchKernelGGL(k_compact_write, dim3((unsigned)nb), dim3(kScanThreads), 0, s, mask, n, blk, cells);
-    return hipGetLastError();
-}
-
 // ------------------------------------------------------------------------------------------ raster helpers
-// Fill kernels instead of memset nodes, so that the same sequence can be captured into a graph.
-__global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, uint32_t v, int64_t n) {
-    const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
-    if (i0 + 4 <= n && (reinterpret_cast<uintptr_t>(p + i0) & 15) == 0) {
-        *reinterpret_cast<uint4*>(p + i0) = make_uint4(v, v, v, v);
-    } else {
-        for (int64_t i = i0; i < n && i < i0 + 4; ++i) p[i] = v;
-    }
-}
-
-__global__ __launch_bounds__(256) void k_fill_u64(unsigned long long* __restrict__ p, unsigned long long v,
-                                                  int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = v;
-}
-
-// DEM with a one-texel border replicating the edge texels: (H + 2) x (W + 2), row-major. Its texel
-// (r + 1, c + 1) holds dem[clamp(r)][clamp(c)] for r in [-1, H], c in [-1, W], which is what the clamped
-// bilinear patch reads, so the padded lookup needs no clamps.
-__global__ __launch_bounds__(256) void k_pad_dem(const float* __restrict__ dem, int H, int W,
-                                                 float* __restrict__ out) {
-    // rows over blockIdx.y, columns over blockIdx.x and the threads: no division per texel
-    const int64_t Wp = (int64_t)W + 2;
-    for (int64_t rp = blockIdx.y; rp < (int64_t)H + 2; rp += gridDim.y) {
-        const int64_t r = rp < 1 ? 0 : (rp > H ? H - 1 : rp - 1);
-        const float* __restrict__ src = dem + r * W;
-        float* __restrict__ dst = out + rp * Wp;
-        for (int64_t cp = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; cp < Wp;
-             cp += (int64_t)gridDim.x * blockDim.x) {
-            const int64_t c = cp < 1 ? 0 : (cp > W ? W - 1 : cp - 1);
-            dst[cp] = src[c];
-        }
-    }
-}
-
-// v^2 bits -> speed, in place: vmax = sqrt(max v^2)
+// v^2 bits -> speed, in place: vmax = sqrt(max v^2). Bound by HBM; texels no particle visited (most of a large region)
+// are read and not written back.
 __global__ __launch_bounds__(256) void k_finalize_vmax(uint32_t* __restrict__ bits, int64_t n) {
     const int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * 4;
     if (i0 + 4 <= n && (reinterpret_cast<uintptr_t>(bits + i0) & 15) == 0) {
         uint4 b = *reinterpret_cast<uint4*>(bits + i0);
+        if ((b.x | b.y | b.z | b.w) == 0u) return;  // no particle came here: its zeros are the speeds already
         b.x = __float_as_uint(sqrtf(__uint_as_float(b.x)));
         b.y = __float_as_uint(sqrtf(__uint_as_float(b.y)));
         b.z = __float_as_uint(sqrtf(__uint_as_float(b.z)));
@@ -427,25 +278,6 @@ __global__ __launch_bounds__(256) void k_finalize_vmax(uint32_t* __restrict__ bi
 static unsigned blocks_for(int64_t items, int per_thread) {
     const int64_t threads = (items + per_thread - 1) / per_thread;
     return (unsigned)((threads + 255) / 256);
-}
-
-hipError_t launch_pad_dem(const float* dem, int H, int W, float* out, hipStream_t s) {
-    const int64_t col_blocks = std::min<int64_t>(((int64_t)W + 2 + 1023) / 1024, 1024);  // ~4 texels per thread
-    const int64_t row_blocks = std::min<int64_t>((int64_t)H + 2, 65535);
-    hipLaunchKernelGGL(k_pad_dem, dim3((unsigned)col_blocks, (unsigned)row_blocks), dim3(256), 0, s, dem, H, W, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_fill_u32(uint32_t* p, uint32_t v, int64_t n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill_u32, dim3(blocks_for(n, 4)), dim3(256), 0, s, p, v, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_fill_u64(unsigned long long* p, unsigned long long v, int64_t n, hipStream_t s) {
-    if (n <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_fill_u64, dim3(blocks_for(n, 1)), dim3(256), 0, s, p, v, n);
-    return hipGetLastError();
 }
 
 // ------------------------------------------------------------------------------------------ mipmap

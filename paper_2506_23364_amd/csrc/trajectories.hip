@@ -676,161 +676,6 @@ void k_trajectories(TrajArgs a) {
     if (probe && threadIdx.x == 0) probe[2] = __builtin_amdgcn_s_memrealtime();
 }
 
-// ------------------------------------------------------------------------------------------ start records
-
-__global__ __launch_bounds__(256) void k_start_records(const float* __restrict__ dem, int H, int W, uint32_t mult,
-                                                       const int32_t* __restrict__ cells,
-                                                       const int32_t* __restrict__ n_cells, int64_t cap,
-                                                       StartRec* __restrict__ starts) {
-    const int64_t n = min((int64_t)*n_cells, cap);  // records of the first `cap` cells at most
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
-        starts[i] = start_state(dem, H, W, mult, (uint32_t)cells[i]);
-}
-
-hipError_t launch_start_records(const float* dem, int H, int W, int mult, const int32_t* cells,
-                                const int32_t* n_cells, int64_t n, StartRec* starts, hipStream_t s) {
-    const int64_t blocks = (n + 255) / 256;
-    hipLaunchKernelGGL(k_start_records, dim3((unsigned)(blocks < 4096 ? (blocks > 0 ? blocks : 1) : 4096)), dim3(256),
-                       0, s, dem, H, W, (uint32_t)mult, cells, n_cells, n, starts);
-    return hipGetLastError();
-}
-
-// ------------------------------------------------------------------------------------------ run table
-
-// One block: per run, derived constants and slot counts, then the exclusive scan of the padded slot
-// counts. A run with an index out of range or invalid parameters gets no slots and status != 0.
-__global__ __launch_bounds__(1024) void k_setup_runs(const RunSpec* __restrict__ specs,
-                                                     const ::avl_params* __restrict__ params, uint32_t n_params,
-                                                     RunSpec one_spec, ::avl_params one_param,
-                                                     const int32_t* __restrict__ n_cells_per_scen, uint32_t n_scen,
-                                                     uint32_t n_tiles, uint32_t n_runs, int32_t H, int32_t W,
-                                                     float cs, uint32_t P, int32_t batched,
-                                                     RunConst* __restrict__ runs,
-                                                     unsigned long long* __restrict__ run_off,
-                                                     int32_t* __restrict__ status, int64_t cap_cells,
-                                                     int32_t* __restrict__ rec_run) {
-    __shared__ unsigned long long wsum[1024 / kWave];
-    const uint32_t per_thread = (n_runs + 1023) / 1024;
-    const uint32_t b0 = threadIdx.x * per_thread;
-    const uint64_t HW = (uint64_t)H * W;
-    unsigned long long local = 0;
-    for (uint32_t k = 0; k < per_thread; ++k) {
-        const uint32_t r = b0 + k;
-        if (r >= n_runs) break;
-        const RunSpec sp = specs ? specs[r] : one_spec;
-        int32_t bad = 0;
-        if (sp.tile >= n_tiles || sp.scenario >= n_scen || (specs && sp.param >= n_params)) bad = 1;
-        ::avl_params p = one_param;
-        if (!bad && specs) p = params[sp.param];
-        if (!bad) {
-            const bool ok = __builtin_isfinite(p.mu) && p.mu >= 0.0f && !__builtin_isnan(p.xi) && p.xi > 0.0f &&
-                            __builtin_isfinite(p.flow_height) && p.flow_height > 0.0f && p.persistence >= 0.0f &&
-                            p.persistence <= 1.0f && __builtin_isfinite(p.randomness) && p.randomness >= 0.0f &&
-                            __builtin_isfinite(p.step_cells) && p.step_cells > 0.0f && p.step_cells <= 16.0f &&
-                            __builtin_isfinite(p.tan_alpha) && p.flags == 0u;
-            if (!ok) bad = 2;
-        }
-        if (!bad && cap_cells >= 0 && (int64_t)n_cells_per_scen[sp.scenario] > cap_cells) bad = 3;
-        RunConst c{};
-        // derived constants, binary32, in this order
-        const float g = 9.81f;
-        const float g2 = g + g;
-        c.per = p.persistence;
-        c.Q = 1.0f - c.per;
-        c.rnd = p.randomness;
-        c.L = p.step_cells;
-        const float dl = c.L * cs;
-        c.dl2 = dl * dl;
-        c.mdl = p.mu * dl;
-        c.cd = g2 / (p.xi * p.flow_height);
-        c.use_alpha = p.tan_alpha >= 0.0f ? 1u : 0u;
-        c.tca = p.tan_alpha * cs;
-        c.key0 = (uint32_t)sp.seed;
-        c.key1 = (uint32_t)(sp.seed >> 32);
-        c.run = sp.run_id;
-        c.dem_off = (uint32_t)(sp.tile * HW);
-        c.pad_off = (uint32_t)(sp.tile * (uint64_t)padded_cells(H, W));
-        c.cells_off = (uint32_t)(sp.scenario * HW);
-        c.raster_off = batched ? (uint32_t)(r * HW) : 0u;
-        c.P = P;
-        c.n_slots = bad ? 0ull : (unsigned long long)(uint32_t)n_cells_per_scen[sp.scenario] * P;
-        runs[r] = c;
-        if (status) status[r] = bad;
-        if (!bad && rec_run) atomicMin(rec_run + sp.scenario, (int32_t)r);
-        local += (c.n_slots + kChunk - 1) / kChunk * kChunk;
-    }
-    // exclusive scan of the per-thread sums
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
-    unsigned long long inc = local;
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        const unsigned long long t = __shfl_up(inc, d, kWave);
-        if (lane >= d) inc += t;
-    }
-    if (lane == kWave - 1) wsum[wid] = inc;
-    __syncthreads();
-    unsigned long long before = 0, tot = 0;
-    for (int k = 0; k < 1024 / kWave; ++k) {
-        before += (k < wid) ? wsum[k] : 0ull;
-        tot += wsum[k];
-    }
-    unsigned long long run = before + inc - local;
-    for (uint32_t k = 0; k < per_thread; ++k) {
-        const uint32_t r = b0 + k;
-        if (r >= n_runs) break;
-        run_off[r] = run;
-        run += (runs[r].n_slots + kChunk - 1) / kChunk * kChunk;
-        // every run's atomicMin has completed at the barrier above; read the result past the L1
-        if (rec_run && specs && specs[r].scenario < n_scen && specs[r].tile < n_tiles) {
-            const int32_t first =
-                __hip_atomic_load(rec_run + specs[r].scenario, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            runs[r].use_rec = (first != 0x7FFFFFFF && specs[first].tile == specs[r].tile) ? 1u : 0u;
-        }
-    }
-    if (threadIdx.x == 0) run_off[n_runs] = tot;
-}
-
-hipError_t launch_setup_runs(const RunSpec* specs, const ::avl_params* params, uint32_t n_params, RunSpec one_spec,
-                             ::avl_params one_param, const int32_t* n_cells_per_scen, uint32_t n_scen, uint32_t n_tiles,
-                             uint32_t n_runs, int32_t H, int32_t W, float cell_size, uint32_t P, bool batched,
-                             RunConst* runs, unsigned long long* run_off, int32_t* status, hipStream_t s,
-                             int64_t cap_cells, int32_t* rec_run) {
-    hipLaunchKernelGGL(k_setup_runs, dim3(1), dim3(1024), 0, s, specs, params, n_params, one_spec, one_param,
-                       n_cells_per_scen, n_scen, n_tiles, n_runs, H, W, cell_size, P, batched ? 1 : 0, runs, run_off,
-                       status, cap_cells, rec_run);
-    return hipGetLastError();
-}
-
-// Batch start records: scenario s's cells on the tile of its first valid run, from the padded tile (the
-// same values the trajectory kernel would read, so the same start states).
-__global__ __launch_bounds__(256) void k_batch_records(const RunSpec* __restrict__ specs,
-                                                       const int32_t* __restrict__ rec_run,
-                                                       const int32_t* __restrict__ n_cells_per_scen, uint32_t n_scen,
-                                                       const int32_t* __restrict__ cells, const float* dem_pad, int H,
-                                                       int W, StartRec* __restrict__ starts) {
-    const uint64_t HW = (uint64_t)H * W;
-    const uint32_t Wp = (uint32_t)W + 2u, row_bytes = 4u * Wp;
-    const uint64_t np = (uint64_t)padded_cells(H, W);
-    for (uint32_t sc = blockIdx.y; sc < n_scen; sc += gridDim.y) {
-        const int32_t first = rec_run[sc];
-        if (first == 0x7FFFFFFF) continue;  // no valid run uses this scenario
-        const __amdgpu_buffer_rsrc_t rs =
-            buffer_rsrc(dem_pad + (uint64_t)specs[first].tile * np, (uint32_t)(np * sizeof(float)));
-        const int64_t nc = n_cells_per_scen[sc];
-        for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < nc; i += (int64_t)gridDim.x * blockDim.x)
-            starts[sc * HW + i] = start_state_pad(rs, Wp, row_bytes, W, (uint32_t)cells[sc * HW + i]);
-    }
-}
-
-hipError_t launch_batch_records(const RunSpec* specs, const int32_t* rec_run, const int32_t* n_cells_per_scen,
-                                uint32_t n_scen, const int32_t* cells, const float* dem_pad, int32_t H, int32_t W,
-                                StartRec* starts, hipStream_t s) {
-    const uint32_t gy = n_scen < 1024u ? n_scen : 1024u;
-    hipLaunchKernelGGL(k_batch_records, dim3(64, gy), dim3(256), 0, s, specs, rec_run, n_cells_per_scen, n_scen, cells,
-                       dem_pad, H, W, starts);
-    return hipGetLastError();
-}
-
 // ------------------------------------------------------------------------------------------ variants
 
 namespace {

@@ -1,0 +1,57 @@
+"""The preparation kernels at the edges of their chunks: release-cell lists around 4096 texels per block, 16 bytes per
+thread and the number of blocks up to which no scan of the counts runs; padded DEMs narrower than one 16-byte store;
+ensembles whose tiles start at unaligned addresses."""
+import numpy as np
+import pytest
+
+import oracle
+import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def avl():
+    import paper_2506_23364_amd as m
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return m
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (1, 15), (3, 5), (1, 4095), (64, 64), (17, 241), (241, 17), (2048, 4096),
+                                   (2049, 4096), (2897, 2897)])
+@pytest.mark.parametrize("density", [0.0, 0.02, 1.0])
+def test_release_cells_at_chunk_edges(avl, shape, density):
+    rng = np.random.default_rng(shape[0] * 7 + shape[1])
+    m = (rng.random(shape) < density).astype(np.uint8) * 255
+    cells, n = avl.release_cells(torch.from_numpy(m).cuda())
+    want = np.flatnonzero(m)
+    assert int(n.item()) == want.size
+    assert np.array_equal(cells[:want.size].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (5, 1), (4, 2), (3, 3), (9, 4), (7, 5), (6, 7), (33, 31)])
+def test_narrow_grids(avl, shape):
+    rng = np.random.default_rng(shape[0] * 11 + shape[1])
+    dem = (rng.random(shape) * 20.0).astype(np.float32)
+    mask = np.ones(shape, np.uint8)
+    p = dict(synth.DEFAULT_PARAMS, mu=0.1)
+    ref = oracle.trajectories(dem, mask, 5.0, oracle.make_params(**p), 3, 60, 9)
+    got = avl.trajectories(torch.from_numpy(dem).cuda(), torch.from_numpy(mask).cuda(), 5.0, avl.Params.make(**p), 3, 60, 9)
+    assert np.array_equal(got.counts.cpu().numpy(), ref.counts)
+    np.testing.assert_allclose(got.vmax.cpu().numpy(), ref.vmax, rtol=1e-5, atol=0)
+    assert list(got.stats.cpu().numpy()) == [ref.steps, ref.n_exit, ref.n_stop, ref.n_limit]
+
+
+def test_batch_of_odd_tiles(avl):
+    rng = np.random.default_rng(3)
+    dems = (rng.random((3, 13, 11)) * 30.0).astype(np.float32)
+    masks = (rng.random((2, 13, 11)) < 0.4).astype(np.uint8)
+    p = dict(synth.DEFAULT_PARAMS, mu=0.1)
+    runs = [(t, s, 0, 5 * t + s, 77) for t in range(3) for s in range(2)]
+    r = avl.trajectories_batched(torch.from_numpy(dems).cuda(), torch.from_numpy(masks).cuda(), 5.0,
+                                 avl.params_tensor([p], "cuda"), avl.runs_tensor(runs, "cuda"), 4, 80)
+    for k, (t, s, _, run_id, seed) in enumerate(runs):
+        ref = oracle.trajectories(dems[t], masks[s], 5.0, oracle.make_params(**p), 4, 80, seed, run_id)
+        assert np.array_equal(r.counts[k].cpu().numpy(), ref.counts), k
+        np.testing.assert_allclose(r.vmax[k].cpu().numpy(), ref.vmax, rtol=1e-5, atol=0)
