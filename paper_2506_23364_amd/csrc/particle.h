@@ -67,12 +67,12 @@ __device__ __forceinline__ float div_root(float q, const RootEst& e) {
     return __builtin_fmaf(__builtin_fmaf(-e.s, q0, q), r, q0);
 }
 
-// sqrtf(x) for x >= 0 or NaN: sqrt_est, unless a lane of the wave holds x < 2^-96, an infinity or a NaN, when the
-// whole wave takes sqrtf (a wave-uniform branch, so the common case pays one compare). `big`: no lane's finite x is
-// below 2^-96.
-__device__ __forceinline__ float sqrt_rn(float x, bool big) {
-    const bool odd = big ? !(x < __builtin_inff()) : !(x >= 0x1p-96f && x < __builtin_inff());
-    if (__builtin_expect(__ballot(odd) != 0ull, 0)) return sqrtf(x);
+// sqrtf(x) for x >= 0 or NaN: sqrt_est, unless a lane of the wave holds a value whose bits are below `lo` (those of 2^-96,
+// or 0 where no lane can hold a smaller number than 2^-96), an infinity or a NaN, when the whole wave takes sqrtf (a
+// wave-uniform branch, so the common case pays one compare).
+constexpr uint32_t kRootLo = 0x0F800000u;  // 2^-96
+__device__ __forceinline__ float sqrt_rn(float x, uint32_t lo) {
+    if (__builtin_expect(__ballot(__float_as_uint(x) - lo > 0x7F7FFFFFu - lo) != 0ull, 0)) return sqrtf(x);
     return sqrt_est(x).s;
 }
 

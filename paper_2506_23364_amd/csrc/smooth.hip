@@ -93,7 +93,7 @@ __device__ __forceinline__ StepOut step(State& s, uint32_t n, uint32_t rep, uint
     const Sample s1 = sample(dem, o.x1, o.y1);
     const float dz = s.z - s1.z;
     // dl2 + dz^2 >= dl2: with dl2 >= 2^-96 (a run constant) no lane is below the short form's range
-    const float ds = sqrt_rn(rc.dl2 + dz * dz, rc.dl2 >= 0x1p-96f);
+    const float ds = sqrt_rn(rc.dl2 + dz * dz, rc.dl2 >= 0x1p-96f ? 0u : kRootLo);
     const float num = s.v2 + g2 * (dz - rc.mdl);
     const bool pos = num > 0.0f;
     const float aa = rc.cd * ds;

@@ -18,7 +18,7 @@
 //    held by other cells goes straight to the raster. A visit that ended is accumulated in the next iteration,
 //    while that iteration's heights are on their way, so the table's LDS round trips are hidden behind the
 //    gather (3 % of the large passes).
-//  - An epoch is a budget of kFlush x (waves per block) wave-iterations that the block's waves claim one
+//  - An epoch is a budget of kFlush x (waves per block) wave-iterations that the block's waves claim two
 //    at a time from an LDS counter, so a wave that runs faster than its neighbours does more of them and
 //    every wave reaches the boundary within about one iteration of the others (a fixed count per wave
 //    left the fast waves waiting at the first barrier for 15-25 % of their time).
@@ -101,7 +101,7 @@ struct Control {
     uint32_t busy[2];             // waves with work left, per epoch parity
     uint32_t part, tried, empty;  // the window's own walk over the XCD partitions
     uint32_t dry;                 // the tail probe has seen the block run out of slots
-    uint32_t iters;               // wave-iterations of the epoch's budget claimed so far
+    uint32_t iters;               // pairs of wave-iterations of the epoch's budget claimed so far
     unsigned long long left;      // slots left in the partition after the window's last top-up
     unsigned long long st[4];     // single run: the block's statistics, summed when its waves are done
 };
@@ -187,52 +187,62 @@ void k_trajectories(TrajArgs a) {
         for (int i = 3; i >= 0; --i) e = t[i] == v ? i : e;
         return e;
     };
-    auto claim = [&](uint32_t key) -> int {
-        uint32_t at = bucket(key, 0x9E3779u);
-        u32x4 t = lds_ld4(tb.tag + at);
-        int i = first_of(t, key);
-        if (i < 0) {
-            // the common claim: the bucket's first empty slot, taken by this key
-            i = first_of(t, kEmpty);
-            uint32_t old = kEmpty;
-            if (i >= 0) old = atomicCAS(tb.tag + at + i, kEmpty, key);
-            if (i < 0 || (old != kEmpty && old != key)) {
-                const uint32_t first = at;
-                i = -1;
+    // The claim past the first try: the key's two buckets, a compare-and-swap per empty candidate. Each failed one means
+    // that the slot was filled meanwhile, so eight rounds see every candidate.
+    auto claim_slow = [&](uint32_t key) -> int {
+        const uint32_t first = bucket(key, 0x9E3779u);
+        uint32_t at = first;
 #pragma unroll 1
-                for (int tries = 0; tries < 8; ++tries) {
-                    t = lds_ld4(tb.tag + at);
-                    i = first_of(t, key);
-                    if (i >= 0) break;
-                    i = first_of(t, kEmpty);
-                    if (i >= 0) {
-                        old = atomicCAS(tb.tag + at + i, kEmpty, key);
-                        if (old == kEmpty || old == key) break;
-                        i = -1;
-                    } else if (at == first) {
-                        at = bucket(key, 0xC2B2AEu) ^ 4u;
-                    } else {
-                        break;
+        for (int tries = 0; tries < 8; ++tries) {
+            const u32x4 t = lds_ld4(tb.tag + at);
+            int i = first_of(t, key);
+            if (i >= 0) return (int)at + i;
+            i = first_of(t, kEmpty);
+            if (i >= 0) {
+                const uint32_t old = atomicCAS(tb.tag + at + i, kEmpty, key);
+                if (old == kEmpty || old == key) return (int)at + i;
+            } else if (at == first) {
+                at = bucket(key, 0xC2B2AEu) ^ 4u;
+            } else {
+                break;
+            }
+        }
+        return -1;
+    };
+    // The visit that ended in the lane's previous iteration: its cell (kEmpty: none) and largest v^2. All lanes run the
+    // bucket read and its compares; a branch is taken by the whole wave, for the lanes that claim and that overflow.
+    uint32_t leave_key = kEmpty, leave_bits = 0;
+    auto accumulate = [&]() {
+        const bool has = leave_key != kEmpty;
+        if (__ballot(has) == 0ull) return;
+        const uint32_t at = bucket(leave_key, 0x9E3779u);
+        const u32x4 t = lds_ld4(tb.tag + at);
+        const int m = first_of(t, leave_key);
+        int sl = m < 0 ? -1 : (int)at + m;
+        if (__ballot(has && m < 0) != 0ull) {
+            if (has && m < 0) {
+                // the common claim: the bucket's first empty slot, taken by this key
+                const int e = first_of(t, kEmpty);
+                if (e >= 0) {
+                    const uint32_t old = atomicCAS(tb.tag + at + e, kEmpty, leave_key);
+                    if (old == kEmpty || old == leave_key) sl = (int)at + e;
+                }
+            }
+            if (__ballot(has && sl < 0) != 0ull) {
+                if (has && sl < 0) {
+                    sl = claim_slow(leave_key);
+                    if (sl < 0) {
+                        atomicAdd(counts + leave_key, 1u);
+                        if (leave_bits) global_max(vmax2 + leave_key, leave_bits);
                     }
                 }
             }
         }
-        return i < 0 ? -1 : (int)at + i;
-    };
-    // The visit that ended in the wave's previous iteration: its cell and largest v^2.
-    uint32_t leave_key = kEmpty, leave_bits = 0;
-    auto accumulate = [&]() {
-        if (leave_key != kEmpty) {
-            const int sl = claim(leave_key);
-            if (sl >= 0) {
-                atomicAdd(tb.cnt + sl, 1u);
-                if (leave_bits) atomicMax(tb.vmx + sl, leave_bits);
-            } else {
-                atomicAdd(counts + leave_key, 1u);
-                if (leave_bits) global_max(vmax2 + leave_key, leave_bits);
-            }
-            leave_key = kEmpty;
+        if (has && sl >= 0) {
+            atomicAdd(tb.cnt + sl, 1u);
+            atomicMax(tb.vmx + sl, leave_bits);
         }
+        leave_key = kEmpty;
     };
 
     // Shifts the window past the slots handed out in the epoch that ended and tops it up with a new
@@ -326,8 +336,9 @@ void k_trajectories(TrajArgs a) {
 
     // lane state
     bool alive = false;
-    float x = 0, y = 0, z = 0, gx = 0, gy = 0, dx = 0, dy = 0, v2 = 0, x0 = 0, y0 = 0, zr = 0, cmax2 = 0;
-    uint32_t rep = 0, cell_id = 0, spare_x = 0, spare_y = 0, cur = 0;
+    // (a lane without a particle keeps a unit gradient and direction: it runs the steps too, see below)
+    float x = 0, y = 0, z = 0, gx = 1, gy = 0, dx = 1, dy = 0, v2 = 0, x0 = 0, y0 = 0, zr = 0, cmax2 = 0;
+    uint32_t rep = 0, cell_id = 0, cur = 0;
     uint32_t rk = ~0u;  // recording: index of the lane's particle in the recorded range, ~0 if outside it
     auto rec_point = [&](uint32_t m, float px, float py, float pv2) {
         if constexpr (kRec) {
@@ -350,8 +361,81 @@ void k_trajectories(TrajArgs a) {
     };
 
 
-    constexpr uint32_t kBudget = (uint32_t)kFlush * (uint32_t)(kBlock / kWave);  // wave-iterations per epoch
-    uint32_t wit = 0;  // the wave's iterations so far; a live particle's step count has their parity
+    // One step of every live particle, n the parity of `odd`. Every lane runs the whole step and the outcome selects what
+    // it keeps: a lane at the step limit, leaving the grid or stopping discards its target (an off-grid target's gather
+    // reads through the buffer's bounds check, so it cannot fault), and a lane without a particle discards everything.
+    // Without a branch around the step or per outcome the compiler copies no particle state at joins, and a wave with
+    // few lanes left, which decides when a pass ends, has no branch to wait for.
+    auto step = [&](uint32_t ux, uint32_t uy) {
+        const RunConst& R = rc;
+        const float rx = signed_unit(ux), ry = signed_unit(uy);
+        steer(dx, dy, gx, gy, R.per, R.Q, R.rnd, rx, ry);
+        const float x1 = x + R.L * dx;
+        const float y1 = y + R.L * dy;
+        const PatchLoad pl = bilinear_pad_load(dem_rs, Wp, row_bytes, x1, y1);
+        accumulate();  // the previous step's visit, while the heights are on their way
+        const float fc1 = floorf(x1), fr1 = floorf(y1);
+        const bool lim = n >= a.S;
+        const bool inside = fc1 >= 0.0f && fc1 < fW && fr1 >= 0.0f && fr1 < fH;
+        const bool go = alive && !lim, inb = go && inside;
+        const Sample s1 = bilinear_pad_value(pl);
+        const float dz = z - s1.z;
+        // dl2 + dz^2 >= dl2: with dl2 >= 2^-96 (a run constant) no lane is below the short form's range
+        const float ds = sqrt_rn(R.dl2 + dz * dz, R.dl2 >= 0x1p-96f ? 0u : kRootLo);
+        const float num = v2 + a.g2 * (dz - R.mdl);
+        bool stop = !(num > 0.0f);
+        const float v2n = num / (1.0f + R.cd * ds);
+        if (kAlpha && R.use_alpha) {
+            float ax0 = x0, ay0 = y0, azr = zr;
+            if (kBatch) {  // the release cell's centre and the height sampled there
+                const uint32_t rr = udiv(cell_id, a.wdiv), cc = cell_id - rr * (uint32_t)W;
+                ax0 = (float)cc + 0.5f;
+                ay0 = (float)rr + 0.5f;
+                azr = bilinear_pad(dem_rs, Wp, row_bytes, ax0, ay0).z;
+            }
+            const float hx = x1 - ax0, hy = y1 - ay0;
+            stop = stop || (azr - s1.z) < R.tca * sqrtf(hx * hx + hy * hy);
+        }
+        const bool acc = inb && !stop;
+        st_limit += (alive && lim) ? 1u : 0u;
+        st_exit += (go && !inside) ? 1u : 0u;
+        st_stop += (inb && stop) ? 1u : 0u;
+        if constexpr (kRec) {
+            if (alive) {
+                if (lim)
+                    rec_end(0u);
+                else if (!inside)
+                    rec_end(1u);
+                else if (stop) {
+                    rec_point(n + 1u, x1, y1, 0.0f);
+                    rec_end(2u);
+                }
+            }
+        }
+        x = acc ? x1 : x;
+        y = acc ? y1 : y;
+        z = acc ? s1.z : z;
+        gx = acc ? s1.gx : 1.0f;
+        gy = acc ? s1.gy : 0.0f;
+        v2 = acc ? v2n : v2;
+        n += acc ? 1u : 0u;
+        if constexpr (kRec) {
+            if (acc) rec_point(n, x, y, v2);
+        }
+        // row x W as a 24-bit multiply (full rate; a 32-bit one is quarter rate): both factors are below
+        // 2^23 on an accepted grid and nc is used only for a step inside it
+        const uint32_t nc = R.raster_off + __umul24((uint32_t)(int)fr1, (uint32_t)W) + (uint32_t)(int)fc1;
+        const bool change = acc && nc != cur;
+        leave_key = (alive && (change || !acc)) ? cur : kEmpty;
+        leave_bits = __float_as_uint(cmax2);
+        cur = change ? nc : cur;
+        cmax2 = change ? v2 : ((acc && v2 > cmax2) ? v2 : cmax2);
+        alive = acc;
+    };
+
+    // pairs of wave-iterations per epoch: the wave claims two steps at a time, from an even step on
+    constexpr uint32_t kBudget = (uint32_t)(kFlush / 2) * (uint32_t)(kBlock / kWave);
+    static_assert(kFlush % 2 == 0, "an epoch is a whole number of step pairs");
     for (uint32_t epoch = 0;; ++epoch) {
         // the window of this epoch
         const uint64_t wb0 = wave_bcast64(ctl.base[0]), wb1 = wave_bcast64(ctl.base[1]);
@@ -359,8 +443,8 @@ void k_trajectories(TrajArgs a) {
         bool win_out = wl0 + wl1 == 0u;
         bool finished = false;
 
-        // the wave claims each iteration of the epoch's budget one iteration ahead, so the LDS round trip
-        // overlaps the iteration before it
+        // the wave claims each pair of the epoch's budget one pair ahead, so the LDS round trip overlaps the pair
+        // before it
         uint32_t ticket = 0;
         if (lane == 0) ticket = atomicAdd(&ctl.iters, 1u);
         for (;;) {
@@ -372,15 +456,13 @@ void k_trajectories(TrajArgs a) {
                 break;
             }
             if (__builtin_amdgcn_readfirstlane(ticket) >= kBudget) break;
-            const uint32_t it = wit++;
             if (lane == 0) ticket = atomicAdd(&ctl.iters, 1u);
 
             // ---- hand slots to idle lanes in lane order: the reservoir, refilled with the next 64-slot
-            // chunk of the window (else of the queues) when it runs dry. Only on the wave's even iterations:
-            // every particle then starts on an even iteration, so its step parity is the iteration's and
-            // the Philox block (one per two steps) is a uniform branch.
+            // chunk of the window (else of the queues) when it runs dry. Between pairs of steps only, so that one
+            // Philox block (two steps) serves every lane of the pair.
             bool fresh = false;
-            if ((it & 1) == 0 && nidle > 0 && !drained) {
+            if (nidle > 0 && !drained) {
                 // next 64-slot chunk of the window, else of the queues; empty when neither has any left
                 auto next_chunk = [&](uint64_t& base, uint64_t& cend) {
                     base = cend = 0;
@@ -507,94 +589,18 @@ void k_trajectories(TrajArgs a) {
                 }
             }
 
-            // ---- one step of every live particle
-            const RunConst& R = rc;
-            PatchLoad pl{};
-            float x1 = 0, y1 = 0;
-            if (alive) {
-                // Every live lane runs the whole step and the outcome selects what it keeps: a lane at the
-                // step limit, leaving the grid or stopping discards its target (an off-grid target's gather
-                // reads through the buffer's bounds check, so it cannot fault). Without the nested branches
-                // the compiler no longer copies the particle state at every join (5 % of the alpine pass).
-                uint32_t ux, uy;
-                if ((it & 1) == 0) {  // n is even
-                    // the key is wave-uniform: pinning it to scalar registers here makes the round keys
-                    // scalar adds inside the block instead of 20 loop-invariant values hoisted out of the
-                    // loop, spilled to vector lanes and read back by VALU instructions
-                    uint32_t k0 = __builtin_amdgcn_readfirstlane(R.key0);
-                    uint32_t k1 = __builtin_amdgcn_readfirstlane(R.key1);
-                    asm volatile("" : "+s"(k0), "+s"(k1));
-                    const uint4 o = philox4x32_10(n >> 1, rep, cell_id, R.run, k0, k1);
-                    ux = o.x;
-                    uy = o.y;
-                    spare_x = o.z;
-                    spare_y = o.w;
-                } else {
-                    ux = spare_x;
-                    uy = spare_y;
-                }
-                const float rx = signed_unit(ux), ry = signed_unit(uy);
-                steer(dx, dy, gx, gy, R.per, R.Q, R.rnd, rx, ry);
-                x1 = x + R.L * dx;
-                y1 = y + R.L * dy;
-                pl = bilinear_pad_load(dem_rs, Wp, row_bytes, x1, y1);
-            }
-            accumulate();
-            if (alive) {
-                const bool lim = n >= a.S;
-                const float fc1 = floorf(x1), fr1 = floorf(y1);
-                const bool inb = !lim && fc1 >= 0.0f && fc1 < fW && fr1 >= 0.0f && fr1 < fH;
-                const Sample s1 = bilinear_pad_value(pl);
-                const float dz = z - s1.z;
-                // dl2 + dz^2 >= dl2: with dl2 >= 2^-96 (a run constant) no lane is below the short form's range
-                const float ds = sqrt_rn(R.dl2 + dz * dz, R.dl2 >= 0x1p-96f);
-                const float num = v2 + a.g2 * (dz - R.mdl);
-                bool stop = !(num > 0.0f);
-                const float v2n = num / (1.0f + R.cd * ds);
-                if (kAlpha && R.use_alpha) {
-                    float ax0 = x0, ay0 = y0, azr = zr;
-                    if (kBatch) {  // the release cell's centre and the height sampled there
-                        const uint32_t rr = udiv(cell_id, a.wdiv), cc = cell_id - rr * (uint32_t)W;
-                        ax0 = (float)cc + 0.5f;
-                        ay0 = (float)rr + 0.5f;
-                        azr = bilinear_pad(dem_rs, Wp, row_bytes, ax0, ay0).z;
-                    }
-                    const float hx = x1 - ax0, hy = y1 - ay0;
-                    stop = stop || (azr - s1.z) < R.tca * sqrtf(hx * hx + hy * hy);
-                }
-                const bool acc = inb && !stop;
-                st_limit += lim ? 1u : 0u;
-                st_exit += (!lim && !inb) ? 1u : 0u;
-                st_stop += (inb && stop) ? 1u : 0u;
-                if constexpr (kRec) {
-                    if (lim)
-                        rec_end(0u);
-                    else if (!inb)
-                        rec_end(1u);
-                    else if (stop) {
-                        rec_point(n + 1u, x1, y1, 0.0f);
-                        rec_end(2u);
-                    }
-                }
-                x = acc ? x1 : x;
-                y = acc ? y1 : y;
-                z = acc ? s1.z : z;
-                gx = acc ? s1.gx : gx;
-                gy = acc ? s1.gy : gy;
-                v2 = acc ? v2n : v2;
-                n += acc ? 1u : 0u;
-                if constexpr (kRec) {
-                    if (acc) rec_point(n, x, y, v2);
-                }
-                // row x W as a 24-bit multiply (full rate; a 32-bit one is quarter rate): both factors are below
-                // 2^23 on an accepted grid and nc is used only for a step inside it
-                const uint32_t nc = R.raster_off + __umul24((uint32_t)(int)fr1, (uint32_t)W) + (uint32_t)(int)fc1;
-                const bool change = acc && nc != cur;
-                leave_key = (change || !acc) ? cur : kEmpty;
-                leave_bits = __float_as_uint(cmax2);
-                cur = change ? nc : cur;
-                cmax2 = change ? v2 : ((acc && v2 > cmax2) ? v2 : cmax2);
-                alive = acc;
+            // ---- two steps of every live particle: particles start here only, so their step count is even and one
+            // Philox block serves both
+            {
+                // the key is wave-uniform: pinning it to scalar registers here makes the round keys
+                // scalar adds inside the block instead of 20 loop-invariant values hoisted out of the
+                // loop, spilled to vector lanes and read back by VALU instructions
+                uint32_t k0 = __builtin_amdgcn_readfirstlane(rc.key0);
+                uint32_t k1 = __builtin_amdgcn_readfirstlane(rc.key1);
+                asm volatile("" : "+s"(k0), "+s"(k1));
+                const uint4 o = philox4x32_10(n >> 1, rep, cell_id, rc.run, k0, k1);
+                step(o.x, o.y);
+                step(o.z, o.w);
             }
         }
         accumulate();
