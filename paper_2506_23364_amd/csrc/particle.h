@@ -337,19 +337,43 @@ __device__ __forceinline__ uint64_t active_blocks(uint64_t total, int block_thre
     return want > (uint64_t)kXcds ? want : (uint64_t)kXcds;
 }
 
+// Partitions of the slot queues that have nothing left, as bits, from one look at all the counters (the wave's first
+// kXcds lanes read one each, past the caches): one round trip to the memory side, where finding it out with an atomic on
+// each counter in turn took eight (a wave or block that ran out of slots stalled 4 to 10 us for it). The counters only
+// grow, so a partition seen empty stays empty; one seen with slots left may be empty by the time they are taken.
+// Called by whole waves.
+__device__ __forceinline__ uint32_t empty_partitions(const unsigned long long* queues, uint64_t total, int lane) {
+    // the larger of the two sizes partitions have: one that is a chunk smaller and just ran out costs one failed take
+    const uint64_t size = (total / kChunk + kXcds - 1) / kXcds * kChunk;
+    uint32_t q = (uint32_t)lane * kQueueStride;
+    asm volatile("" : "+v"(q));  // no register held for the address outside this rare path
+    bool none = false;
+    if (lane < kXcds) none = __hip_atomic_load(queues + q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= size;
+    return (uint32_t)__ballot(none) & ((1u << kXcds) - 1u);
+}
+
+// the first partition after `part`, cyclically, that `gone` does not mark (some partition is unmarked)
+__device__ __forceinline__ uint32_t next_partition(uint32_t part, uint32_t gone) {
+    const uint32_t left = ~gone & ((1u << kXcds) - 1u);
+    const uint32_t turned = ((left << kXcds | left) >> (part + 1u)) & ((1u << kXcds) - 1u);  // bit i: part + 1 + i
+    return (part + 1u + (uint32_t)__builtin_ctz(turned)) % (uint32_t)kXcds;
+}
+constexpr uint32_t kAllGone = (1u << kXcds) - 1u;
+
 // Wave-uniform slot dispenser of the smooth kernels. The first chunks of 64 slots are dealt out without
 // atomics, round-robin over the grid's waves (kStaticShare of the chunks, a whole number of rounds); the
 // rest come from per-XCD queues, the wave starting on its own XCD's partition of the remainder and moving
 // on when it is empty. Device-scope atomics on one counter are serialised at the memory side: taking
 // every chunk from the queues cost each wave 4.5-10 us per take (up to ~150 waves per counter). The
 // counters sit kQueueStride words apart, each in a memory line of its own.
+// A problem of at most two chunks per wave is dealt out whole.
 constexpr uint32_t kStaticShareNum = 3, kStaticShareDen = 4;
 struct Dispenser {
     uint64_t total;      // padded slot count (a multiple of kChunk)
     uint64_t dyn_begin;  // slots below it are dealt out statically
     uint64_t st_next;    // the wave's next static chunk (>= dyn_begin: none left)
     uint64_t st_stride;  // kChunk x the grid's waves
-    uint32_t part, tried;
+    uint32_t part, gone;  // the partition taken from; those known to be empty
     bool queue_empty;
     uint64_t res_next, res_end;
 
@@ -357,12 +381,12 @@ struct Dispenser {
     __device__ __forceinline__ void init(uint64_t total_slots, uint32_t xcd, uint64_t wave, uint64_t waves) {
         total = total_slots;
         const uint64_t chunks = total / kChunk;
-        const uint64_t rounds = waves ? chunks * kStaticShareNum / kStaticShareDen / waves : 0;
-        dyn_begin = rounds * waves * kChunk;
+        const uint64_t rounds = chunks <= 2 * waves ? 2 : chunks * kStaticShareNum / kStaticShareDen / waves;
+        dyn_begin = min(rounds * waves * kChunk, total);
         st_stride = waves * kChunk;
-        st_next = rounds ? wave * kChunk : dyn_begin;
+        st_next = wave * kChunk;
         part = xcd;
-        tried = 0;
+        gone = 0;
         queue_empty = dyn_begin >= total;
         res_next = res_end = 0;
     }
@@ -400,8 +424,12 @@ struct Dispenser {
                     cend = (base + kChunk < pe) ? base + kChunk : pe;
                     break;
                 }
-                part = (part + 1) % kXcds;
-                if (++tried >= (uint32_t)kXcds) queue_empty = true;
+                if (gone == 0u) gone = empty_partitions(queues, rem, lane);  // one look; later failures are races
+                gone |= 1u << part;
+                if (gone == kAllGone)
+                    queue_empty = true;
+                else
+                    part = next_partition(part, gone);
             }
         }
         if ((uint64_t)rank < avail)

@@ -26,8 +26,7 @@ namespace {
 
 constexpr uint32_t kCkpt = 64;        // steps between checkpoints (even: segments start on even steps)
 constexpr int kSmoothBlock = 256;
-constexpr int kBackwardGrid = 1536;   // blocks of the adjoint kernel (its scratch is sized for this): six waves
-                                      // per SIMD; 1024 (four) left the long paths' recompute short of waves
+constexpr int kBackwardGrid = 1536;   // blocks of the adjoint kernel at most (its scratch is sized for this)
 constexpr int kReduceChunk = 4096;    // particles per block of the gradient reduction
 static_assert(kCkpt % 2 == 0, "segments must start on even steps (one Philox block serves two steps)");
 
@@ -36,7 +35,6 @@ enum : int { kAccept = 0, kExit = 1, kStop = 2, kAngle = 3 };
 
 struct State {
     float x, y, z, gx, gy, dx, dy, v2, x0, y0, zr;
-    uint32_t spare_x, spare_y;
 };
 
 struct StepOut {
@@ -64,33 +62,31 @@ __device__ __forceinline__ Sample sample(const PadDem& d, float x, float y) {
     return bilinear_pad(d.rs, d.Wp, d.row_bytes, x, y);
 }
 
-// Step n of the model (the same binary32 operations as the plain pass). Updates s when accepted. `even`
-// is n's parity (a wave-uniform value where every live particle of the wave has the parity of the wave's
-// iteration, which makes the Philox block a uniform branch).
-__device__ __forceinline__ StepOut step(State& s, uint32_t n, uint32_t rep, uint32_t cell_id, const RunConst& rc,
-                                        const PadDem& dem, int H, int W, float g2, bool even) {
-    StepOut o;
-    uint32_t ux, uy;
-    if (even) {
-        const uint4 b = philox4x32_10(n >> 1, rep, cell_id, rc.run, rc.key0, rc.key1);
-        ux = b.x;
-        uy = b.y;
-        s.spare_x = b.z;
-        s.spare_y = b.w;
-    } else {
-        ux = s.spare_x;
-        uy = s.spare_y;
-    }
+// A step of the model (the same binary32 operations as the plain pass) in two parts, so that work that does not need the
+// heights can run while they are on their way: the new direction, the target and the patch's loads; then the outcome,
+// which updates s when the step is accepted. Every lane runs the whole step and the outcome selects what it keeps: a
+// target off the grid is read through the buffer's bounds check, which cannot fault; its values are discarded.
+struct Target {
+    float x1, y1;
+    PatchLoad pl;
+};
+__device__ __forceinline__ Target step_begin(State& s, uint32_t ux, uint32_t uy, const RunConst& rc, const PadDem& dem) {
     const float rx = signed_unit(ux), ry = signed_unit(uy);
     steer(s.dx, s.dy, s.gx, s.gy, rc.per, rc.Q, rc.rnd, rx, ry);
-    o.x1 = s.x + rc.L * s.dx;
-    o.y1 = s.y + rc.L * s.dy;
-    // Every lane runs the whole step and the outcome selects what it keeps (no branch per outcome, so the
-    // compiler copies no state at their joins): a target off the grid is read through the buffer's bounds
-    // check, which cannot fault; its values are discarded.
+    Target t;
+    t.x1 = s.x + rc.L * s.dx;
+    t.y1 = s.y + rc.L * s.dy;
+    t.pl = bilinear_pad_load(dem.rs, dem.Wp, dem.row_bytes, t.x1, t.y1);
+    return t;
+}
+
+__device__ __forceinline__ StepOut step_end(State& s, const Target& t, const RunConst& rc, int H, int W, float g2) {
+    StepOut o;
+    o.x1 = t.x1;
+    o.y1 = t.y1;
     const float fc1 = floorf(o.x1), fr1 = floorf(o.y1);
     const bool inb = fc1 >= 0.0f && fc1 < (float)W && fr1 >= 0.0f && fr1 < (float)H;
-    const Sample s1 = sample(dem, o.x1, o.y1);
+    const Sample s1 = bilinear_pad_value(t.pl);
     const float dz = s.z - s1.z;
     // dl2 + dz^2 >= dl2: with dl2 >= 2^-96 (a run constant) no lane is below the short form's range
     const float ds = sqrt_rn(rc.dl2 + dz * dz, rc.dl2 >= 0x1p-96f ? 0u : kRootLo);
@@ -116,80 +112,102 @@ __device__ __forceinline__ StepOut step(State& s, uint32_t n, uint32_t rep, uint
     return o;
 }
 
-__device__ __forceinline__ void splat_q(unsigned long long* __restrict__ q, int H, int W, float x, float y, float val) {
-    const Corners k = corners(H, W, x, y);
-    const float w00 = (1.0f - k.fx) * (1.0f - k.fy), w01 = k.fx * (1.0f - k.fy);
-    const float w10 = (1.0f - k.fx) * k.fy, w11 = k.fx * k.fy;
-    const float sc = 16777216.0f;  // 2^24
-    atomicAdd(q + (size_t)k.ra * W + k.ca, (unsigned long long)(long long)rintf((val * w00) * sc));
-    atomicAdd(q + (size_t)k.ra * W + k.cb, (unsigned long long)(long long)rintf((val * w01) * sc));
-    atomicAdd(q + (size_t)k.rb * W + k.ca, (unsigned long long)(long long)rintf((val * w10) * sc));
-    atomicAdd(q + (size_t)k.rb * W + k.cb, (unsigned long long)(long long)rintf((val * w11) * sc));
+__device__ __forceinline__ StepOut step(State& s, uint32_t ux, uint32_t uy, const RunConst& rc, const PadDem& dem, int H, int W,
+                                        float g2) {
+    const Target t = step_begin(s, ux, uy, rc, dem);
+    return step_end(s, t, rc, H, W, g2);
 }
 
-// Workgroup table of the forward's deposit: the particles of a block come from neighbouring release cells
-// and come to rest in overlapping cells, so their splats are summed in LDS (int64, order-independent like
-// the raster) and each touched cell reaches the raster with one atomic when the block ends. A corner
-// whose probe window is taken goes to the raster directly.
-constexpr int kDepLog2 = 12;
-constexpr int kDepSlots = 1 << kDepLog2;  // 4096 x (4-byte tag + 8-byte sum) = 48 KB
-constexpr int kDepProbes = 4;
-constexpr uint32_t kDepEmpty = 0xFFFFFFFFu;
+// Philox words of steps n and n + 1 (n even)
+__device__ __forceinline__ uint4 step_words(uint32_t n, uint32_t rep, uint32_t cell_id, const RunConst& rc) {
+    // the key is wave-uniform: pinned to scalar registers, the round keys are scalar adds inside the block
+    uint32_t k0 = __builtin_amdgcn_readfirstlane(rc.key0);
+    uint32_t k1 = __builtin_amdgcn_readfirstlane(rc.key1);
+    asm volatile("" : "+s"(k0), "+s"(k1));
+    return philox4x32_10(n >> 1, rep, cell_id, rc.run, k0, k1);
+}
 
-struct DepTable {
-    uint32_t tag[kDepSlots];
-    unsigned long long val[kDepSlots];
+// Workgroup table of splats: the particles of a block come from neighbouring release cells, so their paths and resting
+// points share cells, and their splats are summed in LDS (int64, order-independent like the raster) before they reach
+// the raster: the deposit once when the block ends, the velocity at each epoch boundary. Device-scope adds straight to
+// the raster are performed at the memory side, at some 30e9 a second: the velocity raster of 9.3e6 steps (four 64-bit
+// adds each) took 1.3 ms. A cell's candidates are the four slots of its bucket, seen in one 16-byte read; a cell that
+// finds them taken goes to the raster directly.
+constexpr uint32_t kDepEmpty = 0xFFFFFFFFu;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+template <int kSlots>
+struct SumTable {
+    alignas(16) uint32_t tag[kSlots];
+    unsigned long long val[kSlots];
 };
 
-__device__ __forceinline__ uint32_t dep_home(uint32_t cell) { return (cell * 2654435761u) >> (32 - kDepLog2); }
-
-// The table's adds name the LDS address space: the compiler would otherwise merge them with the raster's
+// The tables' adds name the LDS address space: the compiler would otherwise merge them with the raster's
 // fallback add into one generic (flat) atomic through a selected pointer, which every later LDS wait and
 // every vector-memory wait then has to wait for.
 typedef __attribute__((address_space(3))) unsigned long long lds_u64;
 __device__ __forceinline__ void lds_add_u64(unsigned long long* p, unsigned long long v) {
     __hip_atomic_fetch_add((lds_u64*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
-
-__device__ __forceinline__ uint32_t dep_tag(DepTable& t, uint32_t k) {
-    return __hip_atomic_load(&t.tag[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+__device__ __forceinline__ u32x4 lds_ld4(const uint32_t* p) {
+    return *(const volatile __attribute__((address_space(3))) u32x4*)(const __attribute__((address_space(3))) uint32_t*)p;
 }
 
-// Adds v to the table slot of `cell` (claimed if a probe finds an empty slot first), else to the raster.
-// `first` is a read of the cell's home slot: slots only ever go from empty to a tag, so a stale read of it
-// is either right or empty, and an empty read is settled by the claim.
-__device__ __forceinline__ void dep_add(DepTable& t, unsigned long long* __restrict__ q, uint32_t cell,
-                                        unsigned long long v, uint32_t first) {
+template <int kSlots>
+__device__ __forceinline__ uint32_t sum_home(uint32_t cell) {
+    return (__umul24((__umul24(cell, 0x9E3779u) >> 8) & 0xFFFFu, (uint32_t)kSlots / 4u) >> 16) * 4u;
+}
+
+// Adds v to the slot of `cell`, claimed if a candidate is empty, else to the raster; t: the tags at `at`, its bucket, read
+// before (slots only go from empty to a tag between two flushes, so an old read is right or shows an empty slot, which
+// the compare-and-swap settles).
+template <int kSlots>
+__device__ __forceinline__ void sum_add(SumTable<kSlots>& tb, unsigned long long* __restrict__ q, uint32_t cell, uint32_t at,
+                                        const u32x4& t, unsigned long long v) {
     if (v == 0ull) return;
-    const uint32_t h = dep_home(cell);
-    for (int p = 0; p < kDepProbes; ++p) {
-        const uint32_t k = (h + (uint32_t)p) & (uint32_t)(kDepSlots - 1);
-        uint32_t cur = p == 0 ? first : dep_tag(t, k);
-        if (cur == kDepEmpty) cur = atomicCAS(&t.tag[k], kDepEmpty, cell);  // the old tag: empty if taken here
-        if (cur == kDepEmpty || cur == cell) {
-            lds_add_u64(&t.val[k], v);
-            return;
+    int i = -1;
+#pragma unroll
+    for (int k = 3; k >= 0; --k) i = t[k] == cell ? k : i;
+    if (i < 0) {
+#pragma unroll 1
+        for (int k = 0; k < 4 && i < 0; ++k) {
+            if (tb.tag[at + k] == kDepEmpty || tb.tag[at + k] == cell) {
+                const uint32_t old = atomicCAS(&tb.tag[at + k], kDepEmpty, cell);
+                if (old == kDepEmpty || old == cell) i = k;
+            }
         }
     }
-    atomicAdd(q + cell, v);
+    if (i >= 0)
+        lds_add_u64(&tb.val[at + i], v);
+    else
+        atomicAdd(q + cell, v);
 }
 
-// splat_q through the block's table; the home slots of the four corners are read together (one LDS round
-// trip instead of four)
-__device__ __forceinline__ void splat_q_table(DepTable& t, unsigned long long* __restrict__ q, int H, int W, float x,
-                                              float y, float val) {
+// fixed point of one splat weight: rint(w * 2^24); `small`: every lane's total is below 2^31, so that the rounded value
+// converts through 32 bits (the 64-bit conversion is some ten instructions)
+__device__ __forceinline__ unsigned long long splat_fixed(float w, bool small) {
+    const float r = rintf(w * 16777216.0f);
+    return small ? (unsigned long long)(long long)(int)r : (unsigned long long)(long long)r;
+}
+
+// bilinear splat of val at (x, y) through a table (the height patch's corners and weights, clamped corners merging)
+template <int kSlots>
+__device__ __forceinline__ void splat(SumTable<kSlots>& tb, unsigned long long* __restrict__ q, int H, int W, float x, float y,
+                                      float val) {
     const Corners k = corners(H, W, x, y);
     const float w00 = (1.0f - k.fx) * (1.0f - k.fy), w01 = k.fx * (1.0f - k.fy);
     const float w10 = (1.0f - k.fx) * k.fy, w11 = k.fx * k.fy;
-    const float sc = 16777216.0f;  // 2^24
     const uint32_t c00 = (uint32_t)(k.ra * W + k.ca), c01 = (uint32_t)(k.ra * W + k.cb);
     const uint32_t c10 = (uint32_t)(k.rb * W + k.ca), c11 = (uint32_t)(k.rb * W + k.cb);
-    const uint32_t f00 = dep_tag(t, dep_home(c00)), f01 = dep_tag(t, dep_home(c01));
-    const uint32_t f10 = dep_tag(t, dep_home(c10)), f11 = dep_tag(t, dep_home(c11));
-    dep_add(t, q, c00, (unsigned long long)(long long)rintf((val * w00) * sc), f00);
-    dep_add(t, q, c01, (unsigned long long)(long long)rintf((val * w01) * sc), f01);
-    dep_add(t, q, c10, (unsigned long long)(long long)rintf((val * w10) * sc), f10);
-    dep_add(t, q, c11, (unsigned long long)(long long)rintf((val * w11) * sc), f11);
+    const uint32_t a00 = sum_home<kSlots>(c00), a01 = sum_home<kSlots>(c01);
+    const uint32_t a10 = sum_home<kSlots>(c10), a11 = sum_home<kSlots>(c11);
+    const u32x4 t00 = lds_ld4(tb.tag + a00), t01 = lds_ld4(tb.tag + a01);
+    const u32x4 t10 = lds_ld4(tb.tag + a10), t11 = lds_ld4(tb.tag + a11);
+    const bool small = __ballot(!(fabsf(val) < 127.0f)) == 0ull;  // 127 x 2^24 < 2^31
+    sum_add(tb, q, c00, a00, t00, splat_fixed(val * w00, small));
+    sum_add(tb, q, c01, a01, t01, splat_fixed(val * w01, small));
+    sum_add(tb, q, c10, a10, t10, splat_fixed(val * w10, small));
+    sum_add(tb, q, c11, a11, t11, splat_fixed(val * w11, small));
 }
 
 // release cell of particle slot `slot`, and the particle's replica index within it
@@ -201,11 +219,14 @@ __device__ __forceinline__ uint64_t cell_of_slot(uint64_t slot, const SmoothArgs
 
 }  // namespace
 
-// kBlk threads per block share one deposit table; a.spl particle slots per lane size the grid of a small
-// problem (its variants: 256 threads at 8 slots per lane suit short paths, larger blocks at 2 long ones).
-template <int kBlk>
+// kBlk threads per block share the tables; a.spl particle slots per lane size the grid of a small problem. With kVel every
+// accepted step also splats the velocity raster, through a table that the block flushes every kVelPairs pairs of steps.
+constexpr int kVelPairs = 16;
+template <int kBlk, bool kVel>
 __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
     if ((uint64_t)blockIdx.x >= active_blocks(a.run_off[1], kBlk, a.spl)) return;  // small problems: fewer blocks
+    constexpr int kDepSlots = kVel ? 1024 : 4096;  // 12 or 48 KB
+    constexpr int kVelSlots = kVel ? 3072 : 4;     // 36 KB
     const int lane = threadIdx.x & (kWave - 1);
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
     const RunConst rc = uniform_run(a.runs[0]);
@@ -219,41 +240,97 @@ __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
         disp.init(total, xcd_id(), (uint64_t)blockIdx.x * wpb + threadIdx.x / kWave, nb * wpb);
     }
     const size_t cplane = (size_t)a.C * a.cap;
-    __shared__ DepTable dep;
+    __shared__ SumTable<kDepSlots> dep;
+    __shared__ SumTable<kVelSlots> vel;
     for (int k = threadIdx.x; k < kDepSlots; k += kBlk) {
         dep.tag[k] = kDepEmpty;
         dep.val[k] = 0ull;
+    }
+    if constexpr (kVel) {
+        for (int k = threadIdx.x; k < kVelSlots; k += kBlk) {
+            vel.tag[k] = kDepEmpty;
+            vel.val[k] = 0ull;
+        }
     }
     __syncthreads();
 
     bool alive = false;
     State s{};
+    s.gx = s.dx = 1.0f;  // a lane without a particle runs the steps too and discards them
     uint32_t n = 0, rep = 0, cell_id = 0;
     uint64_t slot_id = 0;
     float mp = 0.0f;
-    uint64_t st_steps = 0;
+    uint64_t st_acc = 0;
     uint32_t st_exit = 0, st_stop = 0, st_limit = 0;
-    // Particles start on the wave's even iterations only: a live particle's step count then has the parity
-    // of the wave's iteration, so the Philox block (one per two steps) is a uniform branch, and the slot
-    // hand-out runs every other iteration. A particle starts from its release cell's start record (one
-    // load, the mass per particle beside it). The waits for vector memory cover stores as well as loads,
-    // so an end record is written in the iteration after the particle ended, after the hand-out's loads.
-    bool end_pending = false;
+    // the particle that ended in the lane's previous step: its record and its deposit wait for the next step's gather
+    bool ended = false, rests = false;
     uint64_t end_slot = 0;
     uint32_t end_val = 0;
-    auto end_particle = [&](uint32_t why) {
-        end_pending = true;
-        end_slot = slot_id;
-        end_val = (n << 2) | why;
-        alive = false;
+    float end_x = 0, end_y = 0, end_mp = 0;
+    auto finish_ends = [&]() {
+        if (__ballot(ended) == 0ull) return;
+        if (ended) {
+            if (rests) splat(dep, a.dep_q, H, W, end_x, end_y, end_mp);
+            a.end_rec[end_slot] = end_val;
+            ended = false;
+        }
     };
 
-    for (uint32_t wit = 0;; ++wit) {
-        const bool even = (wit & 1u) == 0u;
+    // one step of every live particle; checkpoints only before even steps
+    auto advance = [&](uint32_t ux, uint32_t uy, bool even) {
+        const bool lim = n >= a.S;
         if (even) {
+            const bool ck = alive && !lim && n != 0 && n % kCkpt == 0;  // checkpoint 0 is the release cell's start record
+            if (__ballot(ck) != 0ull && ck) {
+                const size_t at = (size_t)(n / kCkpt) * a.cap + slot_id;
+                a.ck[at] = s.x;
+                a.ck[cplane + at] = s.y;
+                a.ck[2 * cplane + at] = s.dx;
+                a.ck[3 * cplane + at] = s.dy;
+                a.ck[4 * cplane + at] = s.v2;
+            }
+        }
+        const float xp = s.x, yp = s.y, v2p = s.v2;
+        const Target tg = step_begin(s, ux, uy, rc, dd);
+        finish_ends();
+        const StepOut o = step_end(s, tg, rc, H, W, a.g2);
+        const bool acc = alive && !lim && o.outcome == kAccept;
+        const bool over = alive && !acc;
+        if (__ballot(over) != 0ull && over) {
+            const bool stop = !lim && o.outcome == kStop;
+            const float t = stop && v2p > 0.0f ? v2p / (v2p - o.num) : 0.0f;
+            ended = true;
+            rests = lim || o.outcome != kExit;
+            end_x = stop ? xp + t * (o.x1 - xp) : xp;
+            end_y = stop ? yp + t * (o.y1 - yp) : yp;
+            end_mp = mp;
+            end_slot = slot_id;
+            end_val = (n << 2) | (lim ? kEndLimit : o.outcome == kExit ? kEndExit : stop ? kEndStop : kEndAngle);
+            st_limit += lim ? 1u : 0u;
+            st_exit += rests ? 0u : 1u;
+            st_stop += rests && !lim ? 1u : 0u;
+            s.gx = 1.0f;
+            s.gy = 0.0f;
+        }
+        n += acc ? 1u : 0u;
+        if constexpr (kVel) {
+            if (acc) splat(vel, a.vel_q, H, W, s.x, s.y, mp * sqrtf(s.v2));
+        }
+        alive = acc;
+    };
+
+    // Particles start between pairs of steps only, so that one Philox block (two steps) serves every lane of a pair. A
+    // particle starts from its release cell's start record (one load, the mass per particle beside it).
+    for (;;) {
+        bool finished = false;
+        for (int pair = 0; !kVel || pair < kVelPairs; ++pair) {
             const uint64_t idle = __ballot(!alive);
-            if (__popcll(idle) == kWave && disp.drained() && __ballot(end_pending) == 0ull) break;
-            if (idle && !disp.drained()) {
+            const bool drained = disp.drained();
+            if (__popcll(idle) == kWave && drained) {
+                finished = true;
+                break;
+            }
+            if (idle && !drained) {
                 const uint64_t slot = disp.take(a.queues, idle, lane, below);
                 if (!alive && slot < rc.n_slots) {
                     const uint64_t i = cell_of_slot(slot, a, rc.P, &rep);
@@ -272,60 +349,35 @@ __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
                     s.v2 = 0.0f;
                     cell_id = st.cell;
                     slot_id = slot;
+                    st_acc += n;  // the lane's previous particle
                     n = 0;
                     alive = true;
                 }
             }
+            const uint4 o = step_words(n, rep, cell_id, rc);
+            advance(o.x, o.y, true);
+            advance(o.z, o.w, false);
         }
-        if (end_pending) {
-            a.end_rec[end_slot] = end_val;
-            end_pending = false;
+        if constexpr (!kVel) break;
+        __syncthreads();
+        for (int k = threadIdx.x; k < kVelSlots; k += kBlk) {
+            if (vel.tag[k] != kDepEmpty) {
+                if (vel.val[k] != 0ull) atomicAdd(a.vel_q + vel.tag[k], vel.val[k]);
+                vel.tag[k] = kDepEmpty;
+                vel.val[k] = 0ull;
+            }
         }
-        if (!alive) continue;
-        if (n >= a.S) {
-            ++st_limit;
-            splat_q_table(dep, a.dep_q, H, W, s.x, s.y, mp);
-            end_particle(kEndLimit);
-            continue;
-        }
-        if (n != 0 && n % kCkpt == 0) {  // checkpoint 0 is the release cell's start record
-            const size_t at = (size_t)(n / kCkpt) * a.cap + slot_id;
-            a.ck[at] = s.x;
-            a.ck[cplane + at] = s.y;
-            a.ck[2 * cplane + at] = s.dx;
-            a.ck[3 * cplane + at] = s.dy;
-            a.ck[4 * cplane + at] = s.v2;
-        }
-        ++st_steps;
-        const float xp = s.x, yp = s.y, v2p = s.v2;
-        const StepOut o = step(s, n, rep, cell_id, rc, dd, H, W, a.g2, even);
-        if (o.outcome == kAccept) {
-            ++n;
-            if (a.vel_q) splat_q(a.vel_q, H, W, s.x, s.y, mp * sqrtf(s.v2));
-            continue;
-        }
-        if (o.outcome == kExit) {
-            ++st_exit;
-            end_particle(kEndExit);
-        } else if (o.outcome == kStop) {
-            ++st_stop;
-            const float t = v2p > 0.0f ? v2p / (v2p - o.num) : 0.0f;
-            splat_q_table(dep, a.dep_q, H, W, xp + t * (o.x1 - xp), yp + t * (o.y1 - yp), mp);
-            end_particle(kEndStop);
-        } else {
-            ++st_stop;
-            splat_q_table(dep, a.dep_q, H, W, xp, yp, mp);
-            end_particle(kEndAngle);
-        }
+        if (!__syncthreads_or(finished ? 0 : 1)) break;
     }
+    finish_ends();
     // every wave of the block is done: the table's sums go to the raster, and the statistics, summed over
     // the block in LDS, go to the four counters with one atomic each per block (the counters share a
-    // memory line, where device-scope atomics serialise)
+    // memory line, where device-scope atomics serialise). Steps: the accepted ones, the exits and the stops.
     __shared__ unsigned long long bst[4];
     if (threadIdx.x < 4) bst[threadIdx.x] = 0ull;
     __syncthreads();
-    const uint64_t s0 = wave_sum64(st_steps), s1 = wave_sum64(st_exit), s2 = wave_sum64(st_stop);
-    const uint64_t s3 = wave_sum64(st_limit);
+    const uint64_t s1 = wave_sum64(st_exit), s2 = wave_sum64(st_stop);
+    const uint64_t s0 = wave_sum64(st_acc + n) + s1 + s2, s3 = wave_sum64(st_limit);
     if (lane == 0) {
         lds_add_u64(&bst[0], s0);
         lds_add_u64(&bst[1], s1);
@@ -407,8 +459,10 @@ __global__ __launch_bounds__(kSmoothBlock) void k_smooth_backward(SmoothArgs a) 
             n0 = c_last < 0 ? 0u : (uint32_t)c_last * kCkpt;
             // segments start at checkpoints, multiples of kCkpt (even): the step's parity is that of the trip
             // count, the same for every lane still in the loop
+            uint4 words{};
             for (uint32_t t = 0; n0 + t < n_end; ++t) {
-                const StepOut o = step(s, n0 + t, rep, cell_id, rc, dd, H, W, a.g2, (t & 1u) == 0u);
+                if ((t & 1u) == 0u) words = step_words(n0 + t, rep, cell_id, rc);
+                const StepOut o = step(s, (t & 1u) ? words.z : words.x, (t & 1u) ? words.w : words.y, rc, dd, H, W, a.g2);
                 a.scratch[(size_t)t * T + gtid] = make_float2(o.a, s.v2);
             }
             float px = s.x, py = s.y;
@@ -416,7 +470,8 @@ __global__ __launch_bounds__(kSmoothBlock) void k_smooth_backward(SmoothArgs a) 
             bool stop = false;
             if (reason == kEndStop) {
                 const float xp = s.x, yp = s.y, v2p = s.v2;
-                const StepOut o = step(s, n_end, rep, cell_id, rc, dd, H, W, a.g2, (n_end & 1u) == 0u);
+                if ((n_end & 1u) == 0u) words = step_words(n_end, rep, cell_id, rc);
+                const StepOut o = step(s, (n_end & 1u) ? words.z : words.x, (n_end & 1u) ? words.w : words.y, rc, dd, H, W, a.g2);
                 const float t = v2p > 0.0f ? v2p / (v2p - o.num) : 0.0f;
                 px = xp + t * (o.x1 - xp);
                 py = yp + t * (o.y1 - yp);
@@ -453,7 +508,8 @@ __global__ __launch_bounds__(kSmoothBlock) void k_smooth_backward(SmoothArgs a) 
                     if (c != c_last) {
                         load(c);
                         for (uint32_t t = 0; c0 + t < c1; ++t) {
-                            const StepOut o = step(s, c0 + t, rep, cell_id, rc, dd, H, W, a.g2, (t & 1u) == 0u);
+                            if ((t & 1u) == 0u) words = step_words(c0 + t, rep, cell_id, rc);
+                            const StepOut o = step(s, (t & 1u) ? words.z : words.x, (t & 1u) ? words.w : words.y, rc, dd, H, W, a.g2);
                             a.scratch[(size_t)t * T + gtid] = make_float2(o.a, s.v2);
                         }
                     }
@@ -674,17 +730,17 @@ struct SmoothVariant {
 constexpr SmoothVariant kFwdVariants[] = {{256, 8}, {1024, 2}, {512, 2}, {1024, 1}, {256, 2}, {512, 4}};
 constexpr uint32_t kBwdSpl[] = {8, 2, 1, 4};
 
-template <int kBlk>
+template <int kBlk, bool kVel>
 void launch_fwd(const SmoothArgs& a, hipStream_t s) {
     int dev = 0, cus = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
         cus = 256;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&k_smooth_forward<kBlk>),
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(&k_smooth_forward<kBlk, kVel>),
                                                      kBlk, 0) != hipSuccess ||
         per_cu <= 0)
         per_cu = 1;
-    hipLaunchKernelGGL(k_smooth_forward<kBlk>, dim3(cus * per_cu), dim3(kBlk), 0, s, a);
+    hipLaunchKernelGGL((k_smooth_forward<kBlk, kVel>), dim3(cus * per_cu), dim3(kBlk), 0, s, a);
 }
 
 }  // namespace
@@ -697,9 +753,9 @@ hipError_t launch_smooth_forward(const SmoothArgs& a, int variant, hipStream_t s
     SmoothArgs b = a;
     b.spl = kFwdVariants[variant].spl;
     switch (kFwdVariants[variant].block) {
-        case 1024: launch_fwd<1024>(b, s); break;
-        case 512: launch_fwd<512>(b, s); break;
-        default: launch_fwd<256>(b, s); break;
+        case 1024: b.vel_q ? launch_fwd<1024, true>(b, s) : launch_fwd<1024, false>(b, s); break;
+        case 512: b.vel_q ? launch_fwd<512, true>(b, s) : launch_fwd<512, false>(b, s); break;
+        default: b.vel_q ? launch_fwd<256, true>(b, s) : launch_fwd<256, false>(b, s); break;
     }
     return hipGetLastError();
 }
