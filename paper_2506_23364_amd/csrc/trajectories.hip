@@ -96,10 +96,10 @@ struct Table {
 // share; it changes only between the barriers of an epoch boundary.
 struct Control {
     unsigned long long base[2];   // the window: two ranges of consecutive slots, taken in order
-    uint32_t len[2];              // their lengths (multiples of 64)
-    uint32_t take;                // window slots handed out this epoch (grows by 64 per take)
+    uint32_t len[2];              // their lengths (multiples of 64 in a batch)
+    uint32_t take;                // window slots handed out this epoch
     uint32_t busy[2];             // waves with work left, per epoch parity
-    uint32_t part, tried, empty;  // the window's own walk over the XCD partitions
+    uint32_t part, gone, empty;   // the window's own walk over the XCD partitions, those known to be empty
     uint32_t dry;                 // the tail probe has seen the block run out of slots
     uint32_t iters;               // pairs of wave-iterations of the epoch's budget claimed so far
     unsigned long long left;      // slots left in the partition after the window's last top-up
@@ -151,23 +151,34 @@ void k_trajectories(TrajArgs a) {
         tb.vmx[k] = 0u;
     }
 
-    // Takes up to `len` consecutive slots from the XCD queues, starting with this XCD's partition and
-    // moving on when it is empty; [base, end) is empty once every partition is. Single lane.
-    // `left` receives what remained of the partition after the take.
-    auto take_global = [&](uint32_t& part, uint32_t& tried, uint32_t& empty, uint32_t len, uint64_t& base,
+    // A problem of at most a slot per lane runs out of slots at once, and the look at all the counters saves its waves a
+    // walk over them (sweep of 94,000 paths 140 -> 132 us); in a larger one, where slots run out late and unevenly, the
+    // walk measured faster (3.8e6 paths 413 us with the look, 376 without).
+    const bool look = total <= (uint64_t)gridDim.x * kBlock;
+
+    // Takes up to `len` consecutive slots from the XCD queues, starting with this XCD's partition and moving on to one
+    // that has slots left when it is empty; [base, end) is empty once every partition is. A whole wave calls it, with
+    // wave-uniform arguments. `left` receives what remained of the partition after the take.
+    auto take_global = [&](uint32_t& part, uint32_t& gone, uint32_t& empty, uint32_t len, uint64_t& base,
                            uint64_t& end, uint64_t& left) {
         base = end = left = 0;
         while (!empty) {
             const uint64_t pb = part_begin(total, part), pe = part_begin(total, part + 1);
-            const uint64_t got = atomicAdd(a.queues + part * kQueueStride, (unsigned long long)len);
+            uint64_t got = 0;
+            if (lane == 0) got = atomicAdd(a.queues + part * kQueueStride, (unsigned long long)len);
+            got = wave_bcast64(got);
             if (pb + got < pe) {
                 base = pb + got;
                 end = (base + len < pe) ? base + len : pe;
                 left = pe - end;
                 return;
             }
-            part = (part + 1) % kXcds;
-            if (++tried >= (uint32_t)kXcds) empty = 1u;
+            if (look && gone == 0u) gone = empty_partitions(a.queues, total, lane);  // later failures are races
+            gone |= 1u << part;
+            if (gone == kAllGone)
+                empty = 1u;
+            else
+                part = next_partition(part, gone);
         }
     };
 
@@ -246,56 +257,67 @@ void k_trajectories(TrajArgs a) {
     };
 
     // Shifts the window past the slots handed out in the epoch that ended and tops it up with a new
-    // range when the second range has been reached. Thread 0, between the barriers of a boundary.
+    // range when the second range has been reached. The block's first wave, between the barriers of a boundary.
     // The first range is at most half of the block's fair share of its partition (rounded up to a chunk): the blocks that
     // come first otherwise take kSuper slots each, and of a problem of one slot per lane they took four times their
     // share while the blocks after them found none (314,576 paths of 130 steps in 512-thread blocks: 1.4 ms, with the half share 0.60 ms).
     const uint64_t first_div = 2ull * max(1ull, (unsigned long long)active / kXcds);
     const uint64_t guide_div = 2ull * max(1u, gridDim.x / (uint32_t)kXcds);  // 2 x blocks per XCD
     auto refill_window = [&](bool first) {
+        uint64_t b0 = 0, b1 = 0, left = 0;
+        uint32_t l0 = 0, l1 = 0, t = 0, part = xcd, gone = 0, empty = total == 0 ? 1u : 0u;
         if (first) {
-            ctl.base[0] = ctl.base[1] = 0;
-            ctl.len[0] = ctl.len[1] = 0;
-            ctl.take = 0;
-            ctl.busy[0] = ctl.busy[1] = 0;
-            ctl.part = xcd;
-            ctl.tried = 0;
-            ctl.empty = total == 0 ? 1u : 0u;
-            ctl.left = part_begin(total, xcd + 1) - part_begin(total, xcd);
-            ctl.dry = 0u;
-            ctl.iters = 0u;
-        }
-        const uint32_t l0 = ctl.len[0], l1 = ctl.len[1];
-        const uint32_t t = min(ctl.take, l0 + l1);
-        if (t >= l0) {
-            ctl.base[0] = ctl.base[1] + (t - l0);
-            ctl.len[0] = l1 - (t - l0);
-            ctl.base[1] = 0;
-            ctl.len[1] = 0;
+            left = part_begin(total, xcd + 1) - part_begin(total, xcd);
         } else {
-            ctl.base[0] += t;
-            ctl.len[0] = l0 - t;
+            b0 = wave_bcast64(ctl.base[0]);
+            b1 = wave_bcast64(ctl.base[1]);
+            l0 = uniform_u(ctl.len[0]);
+            l1 = uniform_u(ctl.len[1]);
+            t = min(uniform_u(ctl.take), l0 + l1);
+            part = uniform_u(ctl.part);
+            gone = uniform_u(ctl.gone);
+            empty = uniform_u(ctl.empty);
+            left = wave_bcast64(ctl.left);
         }
-        ctl.take = 0;
-        if (ctl.len[1] == 0u) {
+        if (t >= l0) {
+            b0 = b1 + (t - l0);
+            l0 = l1 - (t - l0);
+            l1 = 0;
+        } else {
+            b0 += t;
+            l0 -= t;
+        }
+        if (l1 == 0u) {
             // guided top-up: a share of what the partition had left, so windows shrink as the queues
             // drain and every block runs out of work at about the same time
-            const uint64_t share = ctl.left / (first ? first_div : guide_div);
+            const uint64_t share = left / (first ? first_div : guide_div);
             const uint32_t want = share >= kSuper ? kSuper : ((uint32_t)share / kChunk + 1u) * kChunk;
-            uint64_t wb = 0, we = 0, left = 0;
-            take_global(ctl.part, ctl.tried, ctl.empty, want, wb, we, left);
-            ctl.base[1] = wb;
-            ctl.len[1] = (uint32_t)(we - wb);
+            uint64_t we = 0;
+            take_global(part, gone, empty, want, b1, we, left);
+            l1 = (uint32_t)(we - b1);
+        }
+        if (lane == 0) {
+            ctl.base[0] = b0;
+            ctl.base[1] = b1;
+            ctl.len[0] = l0;
+            ctl.len[1] = l1;
+            ctl.take = 0;
+            ctl.part = part;
+            ctl.gone = gone;
+            ctl.empty = empty;
             ctl.left = left;
+            ctl.iters = 0u;
+            if (first) {
+                ctl.busy[0] = ctl.busy[1] = 0;
+                ctl.dry = 0u;
+            }
         }
     };
     // tail probe (diagnostics): per block the real-time clock at its start, when it first finds no slot left
     // in its window nor in any queue, and at its end
     unsigned long long* const probe = a.probe ? a.probe + 3 * (size_t)blockIdx.x : nullptr;
-    if (threadIdx.x == 0) {
-        if (probe) probe[0] = __builtin_amdgcn_s_memrealtime();
-        refill_window(true);
-    }
+    if (probe && threadIdx.x == 0) probe[0] = __builtin_amdgcn_s_memrealtime();
+    if (threadIdx.x < kWave) refill_window(true);
     __syncthreads();
 
     // The wave's run: its constants in scalar registers and its padded DEM tile through a buffer
@@ -330,7 +352,7 @@ void k_trajectories(TrajArgs a) {
 
     // wave-uniform slot state: this wave's own walk over the XCD partitions (once the window is spent),
     // and a reservoir of up to 64 slots with the run they belong to
-    uint32_t part = xcd, tried = 0, queue_empty = (total == 0) ? 1u : 0u;
+    uint32_t part = xcd, gone = 0, queue_empty = (total == 0) ? 1u : 0u;
     uint64_t res_next = 0, res_end = 0;
     uint32_t res_run = 0;
 
@@ -441,6 +463,9 @@ void k_trajectories(TrajArgs a) {
         const uint64_t wb0 = wave_bcast64(ctl.base[0]), wb1 = wave_bcast64(ctl.base[1]);
         const uint32_t wl0 = uniform_u(ctl.len[0]), wl1 = uniform_u(ctl.len[1]);
         bool win_out = wl0 + wl1 == 0u;
+        // few slots left: a single run's wave then takes no more from the queues than it has idle lanes, for what it held
+        // in reserve would wait for its own lanes while other waves run out
+        const bool scarce = uniform_u(ctl.empty) != 0u || wave_bcast64(ctl.left) < guide_div * kChunk;
         bool finished = false;
 
         // the wave claims each pair of the epoch's budget one pair ahead, so the LDS round trip overlaps the pair
@@ -458,61 +483,80 @@ void k_trajectories(TrajArgs a) {
             if (__builtin_amdgcn_readfirstlane(ticket) >= kBudget) break;
             if (lane == 0) ticket = atomicAdd(&ctl.iters, 1u);
 
-            // ---- hand slots to idle lanes in lane order: the reservoir, refilled with the next 64-slot
-            // chunk of the window (else of the queues) when it runs dry. Between pairs of steps only, so that one
+            // ---- hand slots to idle lanes in lane order. Between pairs of steps only, so that one
             // Philox block (two steps) serves every lane of the pair.
             bool fresh = false;
             if (nidle > 0 && !drained) {
-                // next 64-slot chunk of the window, else of the queues; empty when neither has any left
-                auto next_chunk = [&](uint64_t& base, uint64_t& cend) {
-                    base = cend = 0;
-                    if (!win_out) {
-                        uint32_t v = 0;
-                        if (lane == 0) v = atomicAdd(&ctl.take, kChunk);
-                        v = __builtin_amdgcn_readfirstlane(v);
-                        // the ranges are multiples of 64 long, so a chunk never straddles them
-                        if (v < wl0) {
-                            base = wb0 + v;
-                            cend = base + min(wl0 - v, kChunk);
-                        } else if (v - wl0 < wl1) {
-                            base = wb1 + (v - wl0);
-                            cend = base + min(wl1 - (v - wl0), kChunk);
-                        } else {
-                            win_out = true;
-                        }
-                    }
-                    if (cend == base && !queue_empty) {
-                        uint64_t gb = 0, ge = 0, gl = 0;
-                        if (lane == 0) take_global(part, tried, queue_empty, kChunk, gb, ge, gl);
-                        base = wave_bcast64(gb);
-                        cend = wave_bcast64(ge);
-                        queue_empty = __builtin_amdgcn_readfirstlane(queue_empty);
-                        part = __builtin_amdgcn_readfirstlane(part);
-                        tried = __builtin_amdgcn_readfirstlane(tried);
-                    }
-                };
                 const int rank = __popcll(idle & below);
                 uint64_t slot = ~0ull;
                 if constexpr (!kBatch) {
-                    // one run: the reservoir's remainder, then a new chunk, in one pass
-                    const uint64_t avail = res_end - res_next;
-                    if (avail >= (uint64_t)nidle) {
+                    // one run: the reservoir's remainder, then as many slots as lanes are idle from the window (which
+                    // may end in its second range), else from the queues
+                    const uint32_t avail = (uint32_t)(res_end - res_next);
+                    if (avail >= (uint32_t)nidle) {
                         slot = res_next + rank;
                         res_next += nidle;
                     } else {
-                        uint64_t base, cend;
-                        next_chunk(base, cend);
-                        if ((uint64_t)rank < avail)
+                        const uint32_t need = (uint32_t)nidle - avail;
+                        uint64_t b1 = 0, b2 = 0;
+                        uint32_t n1 = 0, n2 = 0;
+                        if (!win_out) {
+                            uint32_t v = 0;
+                            if (lane == 0) v = atomicAdd(&ctl.take, need);
+                            v = __builtin_amdgcn_readfirstlane(v);
+                            if (v < wl0) {
+                                b1 = wb0 + v;
+                                n1 = min(need, wl0 - v);
+                                b2 = wb1;
+                                n2 = min(need - n1, wl1);
+                            } else if (v - wl0 < wl1) {
+                                b1 = wb1 + (v - wl0);
+                                n1 = min(need, wl1 - (v - wl0));
+                            } else {
+                                win_out = true;
+                            }
+                        }
+                        if (n1 == 0u && !queue_empty) {
+                            uint64_t e, left;
+                            take_global(part, gone, queue_empty, scarce ? need : max(need, kChunk), b1, e, left);
+                            n1 = (uint32_t)(e - b1);
+                        }
+                        const uint32_t r = (uint32_t)rank - avail;
+                        if ((uint32_t)rank < avail)
                             slot = res_next + rank;
-                        else if (base + (rank - avail) < cend)
-                            slot = base + (rank - avail);
-                        const uint64_t next = base + ((uint64_t)nidle - avail);
-                        res_next = next < cend ? next : cend;
-                        res_end = cend;
+                        else if (r < n1)
+                            slot = b1 + r;
+                        else if (r - n1 < n2)
+                            slot = b2 + (r - n1);
+                        res_next = b1 + min(n1, need);
+                        res_end = b1 + n1;
                     }
                 } else {
-                    // a batch: the same two sources, but a chunk of another run waits in the reservoir
+                    // a batch: the reservoir, refilled with the next 64-slot chunk of the window (else of the queues) when
+                    // it runs dry; empty when neither has any left. A chunk of another run waits in the reservoir
                     // until the wave has no particle of its current run left
+                    auto next_chunk = [&](uint64_t& base, uint64_t& cend) {
+                        base = cend = 0;
+                        if (!win_out) {
+                            uint32_t v = 0;
+                            if (lane == 0) v = atomicAdd(&ctl.take, kChunk);
+                            v = __builtin_amdgcn_readfirstlane(v);
+                            // the ranges are multiples of 64 long, so a chunk never straddles them
+                            if (v < wl0) {
+                                base = wb0 + v;
+                                cend = base + min(wl0 - v, kChunk);
+                            } else if (v - wl0 < wl1) {
+                                base = wb1 + (v - wl0);
+                                cend = base + min(wl1 - (v - wl0), kChunk);
+                            } else {
+                                win_out = true;
+                            }
+                        }
+                        if (cend == base && !queue_empty) {
+                            uint64_t left;
+                            take_global(part, gone, queue_empty, kChunk, base, cend, left);
+                        }
+                    };
                     uint64_t want = idle;  // idle lanes not yet served
 #pragma unroll 1
                     for (int round = 0; round < 2 && want != 0ull; ++round) {
@@ -608,10 +652,9 @@ void k_trajectories(TrajArgs a) {
         // ---- epoch boundary: count the waves with work left, flush the table, refill the window
         if (lane == 0 && !finished) atomicAdd(&ctl.busy[epoch & 1u], 1u);
         __syncthreads();
+        if (threadIdx.x < kWave) refill_window(false);
         if (threadIdx.x == 0) {
             ctl.busy[(epoch + 1) & 1u] = 0u;
-            ctl.iters = 0u;
-            refill_window(false);
             if (probe && !ctl.dry && ctl.empty && ctl.len[0] == 0u) {
                 ctl.dry = 1u;
                 probe[1] = __builtin_amdgcn_s_memrealtime();
