@@ -3,9 +3,8 @@
 // finalize pass of the trajectory pass and the overlay mipmap.
 //
 // These are streaming passes, written for 64-wide wavefronts with every wave touching whole 256-byte
-// stretches of consecutive cells; all but the normals (bound by their correctly rounded arithmetic) are
-// bound by HBM bandwidth.
-#include "avl_internal.h"
+// stretches of consecutive cells, and bound by HBM bandwidth.
+#include "particle.h"
 
 namespace avl {
 
@@ -13,19 +12,62 @@ namespace avl {
 // Block = 64 x 16 texels, 256 threads (one wave per row, four rows per thread); the tile plus a
 // one-texel halo is staged in LDS so every DEM value is read from L2/HBM about once. Gradient: central
 // difference inside, one-sided at the grid edges (the textbook finite difference);
-// n = (-gx, -gy, 1)/sqrt(gx^2 + gy^2 + 1). Each texel takes five correctly rounded divisions, two square
-// roots and an arctangent, so the pass is bound by VALU issue; a thread's four texels are independent
-// chains the compiler interleaves.
+// n = (-gx, -gy, 1)/sqrt(gx^2 + gy^2 + 1). Each texel takes five correctly rounded quotients, two square roots and an
+// arctangent. The quotients share two divisors, so they come from two reciprocals (of the cell size, correctly rounded
+// on the host, and of the root, from the same estimate as the root itself) by one residual step each, and the pass is
+// bound by HBM where the compiler's five divisions bound it by VALU issue (3000 x 5001: 73 -> 64 us).
 // kMask: the release map of the same texels as well (the release-mask pass below on the nz just computed and
 // the staged height, so the map is the one that pass writes from these normals, without reading them back).
 struct MaskArgs {
     float cmin, cmax, zmin, zmax;
     uint8_t* mask;
 };
+struct CellSize {
+    float cs, cs2;    // the texel edge, twice it
+    float rcs, rcs2;  // their reciprocals, correctly rounded
+    int mid;          // both in [2^-40, 2^40]
+};
 constexpr int kNTX = 64, kNTY = 16, kNRows = 4;  // tile columns, tile rows, rows of threads
+
+// The texel's outputs from its height differences dx, dy over sx, sy (reciprocals rx, ry). The short quotients are those
+// of the compiler's divisions (Markstein's residual step from a correctly rounded reciprocal) where no operand, quotient
+// or residual comes near the subnormal or overflow range: a wave with a lane outside takes the divisions.
+__device__ __forceinline__ float4 normal_of(float dx, float dy, float sx, float sy, float rx, float ry, int mid) {
+    auto quotient = [](float a, float b, float r) {
+        const float q = a * r;
+        return __builtin_fmaf(__builtin_fmaf(-b, q, a), r, q);
+    };
+    auto in_range = [](float d, float g) {  // |g| in [2^-60, 2^60], or the difference is 0
+        return d == 0.0f || (__float_as_uint(g) & 0x7FFFFFFFu) - 0x21800000u <= 0x5D800000u - 0x21800000u;
+    };
+    float gx = quotient(dx, sx, rx), gy = quotient(dy, sy, ry);
+    float gg = gx * gx + gy * gy;
+    // 0 < gg < 2^-96 falls outside the short root's range; gg = 0 has the root 0
+    const bool odd = !in_range(dx, gx) || !in_range(dy, gy) || !(gg == 0.0f || gg >= 0x1p-96f);
+    float4 o;
+    if (mid && __builtin_expect(__ballot(odd) == 0ull, 1)) {
+        const dev::RootEst e = dev::sqrt_est(gg + 1.0f);
+        const float r = dev::recip_root(e);
+        o.x = -quotient(gx, e.s, r);
+        o.y = -quotient(gy, e.s, r);
+        o.z = r;
+        o.w = atanf(gg > 0.0f ? dev::sqrt_est(gg).s : 0.0f) * 57.295779513082320876798f;
+    } else {
+        gx = dx / sx;
+        gy = dy / sy;
+        gg = gx * gx + gy * gy;
+        const float l = sqrtf(gg + 1.0f);
+        o.x = -(gx / l);
+        o.y = -(gy / l);
+        o.z = 1.0f / l;
+        o.w = atanf(sqrtf(gg)) * 57.295779513082320876798f;
+    }
+    return o;
+}
+
 template <bool kMask>
-__global__ __launch_bounds__(kNTX * kNRows) void k_normals(const float* __restrict__ dem, int H, int W, float cs,
-                                                           float cs2, float4* __restrict__ out, MaskArgs m) {
+__global__ __launch_bounds__(kNTX * kNRows) void k_normals(const float* __restrict__ dem, int H, int W, CellSize s,
+                                                           float4* __restrict__ out, MaskArgs m) {
     __shared__ float tile[kNTY + 2][kNTX + 2];
     const int tx = threadIdx.x & (kNTX - 1), ty = threadIdx.x / kNTX;
     const int c0 = blockIdx.x * kNTX, r0 = blockIdx.y * kNTY;
@@ -39,31 +81,18 @@ __global__ __launch_bounds__(kNTX * kNRows) void k_normals(const float* __restri
     __syncthreads();
     const int c = c0 + tx;
     if (c >= W) return;
+    // an edge texel's neighbour outside the grid is staged as the texel itself, so the one-sided difference is the
+    // staged one over the single edge
+    const bool ex = c == 0 || c == W - 1;
+    const float sx = ex ? s.cs : s.cs2, rx = ex ? s.rcs : s.rcs2;
 #pragma unroll
     for (int k = 0; k < kNTY / kNRows; ++k) {
         const int r = r0 + ty + k * kNRows;
         if (r >= H) break;
         const int lr = ty + k * kNRows + 1, lc = tx + 1;
-        float gx, gy;
-        if (c == 0)
-            gx = (tile[lr][lc + 1] - tile[lr][lc]) / cs;
-        else if (c == W - 1)
-            gx = (tile[lr][lc] - tile[lr][lc - 1]) / cs;
-        else
-            gx = (tile[lr][lc + 1] - tile[lr][lc - 1]) / cs2;
-        if (r == 0)
-            gy = (tile[lr + 1][lc] - tile[lr][lc]) / cs;
-        else if (r == H - 1)
-            gy = (tile[lr][lc] - tile[lr - 1][lc]) / cs;
-        else
-            gy = (tile[lr + 1][lc] - tile[lr - 1][lc]) / cs2;
-        const float gg = gx * gx + gy * gy;
-        const float l = sqrtf(gg + 1.0f);
-        float4 o;
-        o.x = -(gx / l);
-        o.y = -(gy / l);
-        o.z = 1.0f / l;
-        o.w = atanf(sqrtf(gg)) * 57.295779513082320876798f;
+        const bool ey = r == 0 || r == H - 1;
+        const float4 o = normal_of(tile[lr][lc + 1] - tile[lr][lc - 1], tile[lr + 1][lc] - tile[lr - 1][lc], sx,
+                                   ey ? s.cs : s.cs2, rx, ey ? s.rcs : s.rcs2, s.mid);
         out[(size_t)r * W + c] = o;
         if constexpr (kMask) {
             const float z = tile[lr][lc];  // dem[r][c]: an in-grid texel is staged unclamped
@@ -72,10 +101,19 @@ __global__ __launch_bounds__(kNTX * kNRows) void k_normals(const float* __restri
     }
 }
 
+static CellSize cell_size_of(float cs) {
+    CellSize s;
+    s.cs = cs;
+    s.cs2 = 2.0f * cs;
+    s.rcs = 1.0f / s.cs;
+    s.rcs2 = 1.0f / s.cs2;
+    s.mid = cs >= 0x1p-40f && s.cs2 <= 0x1p40f;
+    return s;
+}
+
 hipError_t launch_normals(const float* dem, int H, int W, float cs, float* out4, hipStream_t s) {
     dim3 grid((W + kNTX - 1) / kNTX, (H + kNTY - 1) / kNTY);
-    const float cs2 = 2.0f * cs;
-    hipLaunchKernelGGL(k_normals<false>, grid, dim3(kNTX * kNRows), 0, s, dem, H, W, cs, cs2,
+    hipLaunchKernelGGL(k_normals<false>, grid, dim3(kNTX * kNRows), 0, s, dem, H, W, cell_size_of(cs),
                        reinterpret_cast<float4*>(out4), MaskArgs{});
     return hipGetLastError();
 }
@@ -83,8 +121,7 @@ hipError_t launch_normals(const float* dem, int H, int W, float cs, float* out4,
 hipError_t launch_normals_mask(const float* dem, int H, int W, float cs, float cmin, float cmax, float zmin,
                                float zmax, float* out4, uint8_t* mask, hipStream_t s) {
     dim3 grid((W + kNTX - 1) / kNTX, (H + kNTY - 1) / kNTY);
-    const float cs2 = 2.0f * cs;
-    hipLaunchKernelGGL(k_normals<true>, grid, dim3(kNTX * kNRows), 0, s, dem, H, W, cs, cs2,
+    hipLaunchKernelGGL(k_normals<true>, grid, dim3(kNTX * kNRows), 0, s, dem, H, W, cell_size_of(cs),
                        reinterpret_cast<float4*>(out4), MaskArgs{cmin, cmax, zmin, zmax, mask});
     return hipGetLastError();
 }
