@@ -311,73 +311,118 @@ static unsigned blocks_for(int64_t items, int per_thread) {
 
 // ------------------------------------------------------------------------------------------ mipmap
 
-// Up to kMipPass levels of the overlay mipmap in one pass. A block owns a 32 x 32 tile of the pass's
-// first output level (a 64 x 64 tile of its input) and every coarser cell of that tile down to 1 x 1:
-// each level halves the previous one rounding up, so the children of a cell never leave the tile.
-// Counts add in 64 bits; speeds (>= 0) take the maximum; cells past a level's edge count as empty.
+// Up to kMipPass levels of the overlay mipmap in one pass, bound by HBM. A wave's lane takes 4 x 4 cells of the input (four
+// 16-byte loads of each raster, 1 KiB contiguous per wave and row), which makes 2 x 2 cells of the first output level and
+// one of the second in registers; a block's 64 x 16 second-level cells are reduced further in LDS. Each level halves the
+// previous one rounding up, so the children of a cell never leave the block's cells. Counts add in 64 bits; speeds (>= 0)
+// take the maximum; cells past a level's edge count as empty. (2 x 2 cells a lane by 4-byte loads, 64 input columns a
+// block: 8192 x 8191 in 195 us, now 174; a copy of its 790 MB takes 151.)
+constexpr int kMipCols = 64, kMipRows = 16;  // second-level cells of a block
+template <typename T>
+struct Vec4 {
+    typedef T type __attribute__((ext_vector_type(4), aligned(sizeof(T))));
+};
+template <typename T>
+struct Vec2 {
+    typedef T type __attribute__((ext_vector_type(2), aligned(sizeof(T))));
+};
+
 template <typename Tin>
 __global__ __launch_bounds__(256) void k_mip(const Tin* __restrict__ cin, const float* __restrict__ vin, int h0, int w0,
                                              int nlev, MipLevels o) {
-    __shared__ unsigned long long sc[32 * 32];
-    __shared__ float sv[32 * 32];
-    const int tr = blockIdx.y * 32, tc = blockIdx.x * 32;
-    for (int k = threadIdx.x; k < 32 * 32; k += 256) {
-        const int r = tr + k / 32, c = tc + k % 32;
-        unsigned long long sum = 0;
-        float mx = 0.0f;
-        if (r < o.h[0] && c < o.w[0]) {
+    __shared__ unsigned long long sc[kMipRows * kMipCols];
+    __shared__ float sv[kMipRows * kMipCols];
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    const int cu = blockIdx.x * kMipCols + lane;
+    const int64_t c0 = 4 * (int64_t)cu;
 #pragma unroll
-            for (int dr = 0; dr < 2; ++dr)
+    for (int k = 0; k < kMipRows / 4; ++k) {
+        const int lr = wid + 4 * k;
+        const int ru = blockIdx.y * kMipRows + lr;
+        const int64_t r0 = 4 * (int64_t)ru;
+        unsigned long long s1[2][2] = {{0, 0}, {0, 0}};
+        float m1[2][2] = {{0.0f, 0.0f}, {0.0f, 0.0f}};
+        if (r0 + 4 <= h0 && c0 + 4 <= w0) {
+            typename Vec4<Tin>::type c[4];
+            typename Vec4<float>::type v[4];
 #pragma unroll
-                for (int dc = 0; dc < 2; ++dc) {
-                    const int rr = 2 * r + dr, cc = 2 * c + dc;
-                    if (rr < h0 && cc < w0) {
-                        const size_t i = (size_t)rr * w0 + cc;
-                        sum += (unsigned long long)cin[i];
-                        mx = fmaxf(mx, vin[i]);
-                    }
+            for (int q = 0; q < 4; ++q) {
+                c[q] = *reinterpret_cast<const typename Vec4<Tin>::type*>(cin + (r0 + q) * w0 + c0);
+                v[q] = *reinterpret_cast<const typename Vec4<float>::type*>(vin + (r0 + q) * w0 + c0);
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+#pragma unroll
+                for (int p = 0; p < 4; ++p) {
+                    s1[q / 2][p / 2] += (unsigned long long)c[q][p];
+                    m1[q / 2][p / 2] = fmaxf(m1[q / 2][p / 2], v[q][p]);
                 }
-            o.c[0][(size_t)r * o.w[0] + c] = sum;
-            o.v[0][(size_t)r * o.w[0] + c] = mx;
+        } else {
+            for (int q = 0; q < 4; ++q)
+                for (int p = 0; p < 4; ++p)
+                    if (r0 + q < h0 && c0 + p < w0) {
+                        s1[q / 2][p / 2] += (unsigned long long)cin[(r0 + q) * w0 + c0 + p];
+                        m1[q / 2][p / 2] = fmaxf(m1[q / 2][p / 2], vin[(r0 + q) * w0 + c0 + p]);
+                    }
         }
-        sc[k] = sum;
-        sv[k] = mx;
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int64_t r = 2 * (int64_t)ru + q, c = 2 * (int64_t)cu, at = r * o.w[0] + c;
+            if (r < o.h[0] && c + 1 < o.w[0]) {
+                *reinterpret_cast<typename Vec2<unsigned long long>::type*>(o.c[0] + at) = {s1[q][0], s1[q][1]};
+                *reinterpret_cast<typename Vec2<float>::type*>(o.v[0] + at) = {m1[q][0], m1[q][1]};
+            } else if (r < o.h[0] && c < o.w[0]) {
+                o.c[0][at] = s1[q][0];
+                o.v[0][at] = m1[q][0];
+            }
+        }
+        const unsigned long long s2 = (s1[0][0] + s1[0][1]) + (s1[1][0] + s1[1][1]);
+        const float m2 = fmaxf(fmaxf(m1[0][0], m1[0][1]), fmaxf(m1[1][0], m1[1][1]));
+        if (nlev > 1 && ru < o.h[1] && cu < o.w[1]) {
+            o.c[1][(int64_t)ru * o.w[1] + cu] = s2;
+            o.v[1][(int64_t)ru * o.w[1] + cu] = m2;
+        }
+        sc[lr * kMipCols + lane] = s2;
+        sv[lr * kMipCols + lane] = m2;
     }
-    __syncthreads();
-    int side = 32;
-    for (int l = 1; l < nlev; ++l) {
-        const int s2 = side / 2;
+    int cols = kMipCols, rows = kMipRows;
+    for (int l = 2; l < nlev; ++l) {
+        __syncthreads();
+        const int c2 = cols / 2, r2 = rows / 2;
         const int t = threadIdx.x;
+        const bool mine = t < c2 * r2;
+        const int i = t / c2, j = t - i * c2;
         unsigned long long sum = 0;
         float mx = 0.0f;
-        const int i = t / s2, j = t - (t / s2) * s2;
-        if (t < s2 * s2) {
+        if (mine) {
 #pragma unroll
             for (int dr = 0; dr < 2; ++dr)
 #pragma unroll
                 for (int dc = 0; dc < 2; ++dc) {
-                    sum += sc[(2 * i + dr) * side + 2 * j + dc];
-                    mx = fmaxf(mx, sv[(2 * i + dr) * side + 2 * j + dc]);
+                    sum += sc[(2 * i + dr) * cols + 2 * j + dc];
+                    mx = fmaxf(mx, sv[(2 * i + dr) * cols + 2 * j + dc]);
                 }
         }
         __syncthreads();
-        if (t < s2 * s2) {
-            sc[i * s2 + j] = sum;
-            sv[i * s2 + j] = mx;
-            const int r = blockIdx.y * s2 + i, c = blockIdx.x * s2 + j;
+        if (mine) {
+            sc[i * c2 + j] = sum;
+            sv[i * c2 + j] = mx;
+            const int r = blockIdx.y * r2 + i, c = blockIdx.x * c2 + j;
             if (r < o.h[l] && c < o.w[l]) {
                 o.c[l][(size_t)r * o.w[l] + c] = sum;
                 o.v[l][(size_t)r * o.w[l] + c] = mx;
             }
         }
-        __syncthreads();
-        side = s2;
+        cols = c2;
+        rows = r2;
     }
 }
+static_assert(kMipPass == 6 && kMipRows >> 4 == 1, "level 6 of a block is one row of cells");
 
 hipError_t launch_mip_pass(const void* cin, bool cin64, const float* vin, int h0, int w0, int nlev,
                            const MipLevels& o, hipStream_t s) {
-    const dim3 grid((unsigned)((o.w[0] + 31) / 32), (unsigned)((o.h[0] + 31) / 32));
+    const dim3 grid((unsigned)(((int64_t)w0 + 4 * kMipCols - 1) / (4 * kMipCols)),
+                    (unsigned)(((int64_t)h0 + 4 * kMipRows - 1) / (4 * kMipRows)));
     if (cin64)
         hipLaunchKernelGGL(k_mip<unsigned long long>, grid, dim3(256), 0, s,
                            static_cast<const unsigned long long*>(cin), vin, h0, w0, nlev, o);
