@@ -299,8 +299,8 @@ int smooth_forward_variants();
 int smooth_backward_variants();
 hipError_t launch_smooth_forward(const SmoothArgs& a, int variant, hipStream_t s);
 hipError_t launch_smooth_backward_kernel(const SmoothArgs& a, int variant, hipStream_t s);
-// the adjoint's reductions after its kernel: dL/dparams and dL/dmass
-hipError_t launch_smooth_reductions(const SmoothArgs& a, const int32_t* n_cells, float* dmass, int64_t n_grid,
+// the adjoint's reductions after its kernel: dL/dparams and dL/dmass (of at most max_cells release cells)
+hipError_t launch_smooth_reductions(const SmoothArgs& a, const int32_t* n_cells, float* dmass, int64_t max_cells,
                                     double* part, double* dparams, hipStream_t s);
 // q0 -> out0 and q1 -> out1 (either pair may be null)
 hipError_t launch_q_to_float(const unsigned long long* q0, float* out0, const unsigned long long* q1, float* out1, int64_t n,

@@ -16,6 +16,8 @@
 // reverse sweep of the v^2 recursion segment by segment (each segment recomputed forward from its
 // checkpoint into a per-lane scratch of (a_k, v^2_{k+1}), then swept backward). Per-particle
 // results are reduced in a fixed order (deterministic).
+#include <algorithm>
+
 #include "particle.h"
 
 namespace avl {
@@ -534,59 +536,132 @@ __global__ __launch_bounds__(kSmoothBlock) void k_smooth_backward(SmoothArgs a) 
 
 // ------------------------------------------------------------------------------------------ reductions
 
-// Sum of the per-particle (dmu, dxi, dh) over particles [0, n): each block sums kReduceChunk particles
-// (16 per thread in order, then a fixed tree) into partial[block]; all in binary64.
-__global__ __launch_bounds__(256) void k_reduce_params(const float* __restrict__ pp, unsigned long long cap,
-                                                       const RunConst* __restrict__ runs, double* __restrict__ part) {
-    __shared__ double sh[3][256];
-    const unsigned long long n = runs[0].n_slots;
+// After the adjoint kernel, one launch: its first a.nb blocks sum the particles' (dmu, dxi, dh), the others the cells'
+// dL/dmass. All sums are binary64 in a fixed order, so the results do not depend on timing. A pass is over in some
+// 200 us, and these sums are bound by the latency of their loads and by their launches: three kernels with one 4-byte load
+// in flight per thread took 33 us for 640,000 particles of 5000 cells, this one takes 10.
+//
+// dL/dparams: a block sums kReduceChunk particles (16 per thread in order, then a fixed tree) into part[block]; the last
+// block to finish sums the blocks that held particles, each thread every 256th in order, then the same tree.
+// dL/dmass of release cell i: (sum over its P particles of sum gD w, in order) / P. A wave takes kMassRows cells and reads
+// them kWave particles at a time, each cell one contiguous stretch, and turns them through LDS so that a lane sums a
+// cell's particles in order; below kMassCols particles a cell, where most lanes of such a load would have no particle, a
+// thread reads its own cell's particles.
+constexpr int kReduceThreads = 256;
+constexpr int kMassRows = 16;
+constexpr uint32_t kMassCols = 16;
+constexpr uint32_t kTicket = 16;  // the word of the queue counters' memory that counts finished blocks; zero at launch
+static_assert(kReduceChunk == 16 * kReduceThreads && kTicket < kQueueStride, "");
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+
+struct ReduceArgs {
+    const float* pp;
+    unsigned long long cap;
+    const RunConst* runs;
+    double* part;  // 3 a.nb
+    double* out;   // 3
+    unsigned long long* queues;
+    uint32_t nb;
+    const int32_t* cells;  // dmass: cells, their number, the raster
+    const int32_t* n_cells;
+    float* dmass;
+};
+
+__device__ __forceinline__ void tree_sum3(double (&sh)[3][kReduceThreads], const double (&acc)[3]) {
+    for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] = acc[q];
+    __syncthreads();
+    for (int d = kReduceThreads / 2; d >= 1; d >>= 1) {
+        if ((int)threadIdx.x < d)
+            for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + d];
+        __syncthreads();
+    }
+}
+
+// The block's part of dL/dparams; true in the block that finished last, whose thread 0 has written a.out.
+__device__ __forceinline__ bool reduce_params(const ReduceArgs& a, double (&sh)[3][kReduceThreads]) {
+    __shared__ uint32_t rank;
+    const unsigned long long n = a.runs[0].n_slots;
+    const uint32_t used = max(1u, (uint32_t)((n + kReduceChunk - 1) / kReduceChunk));  // blocks that hold particles
+    if (blockIdx.x >= used) return false;
     const unsigned long long base = (unsigned long long)blockIdx.x * kReduceChunk + threadIdx.x * 16ull;
     double acc[3] = {0.0, 0.0, 0.0};
-    for (int k = 0; k < 16; ++k) {
-        const unsigned long long i = base + k;
-        if (i < n) {
-            acc[0] += (double)pp[i];
-            acc[1] += (double)pp[cap + i];
-            acc[2] += (double)pp[2 * cap + i];
+    if (base + 16 <= n) {
+        f32x4_any v[3][4];
+#pragma unroll
+        for (int q = 0; q < 3; ++q)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[q][k] = *reinterpret_cast<const f32x4_any*>(a.pp + q * a.cap + base + 4 * k);
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) acc[q] += (double)v[q][k / 4][k % 4];
+    } else {
+        for (unsigned long long i = base; i < n; ++i)
+            for (int q = 0; q < 3; ++q) acc[q] += (double)a.pp[q * a.cap + i];
+    }
+    tree_sum3(sh, acc);
+    if (threadIdx.x == 0) {
+        for (int q = 0; q < 3; ++q) a.part[3 * (size_t)blockIdx.x + q] = sh[q][0];
+        __threadfence();
+        rank = (uint32_t)atomicAdd(a.queues + kTicket, 1ull);
+    }
+    __syncthreads();
+    if (rank != used - 1u) return false;
+    __threadfence();
+    for (int q = 0; q < 3; ++q) acc[q] = 0.0;
+    for (uint32_t b = threadIdx.x; b < used; b += kReduceThreads)
+        for (int q = 0; q < 3; ++q) acc[q] += a.part[3 * (size_t)b + q];
+    tree_sum3(sh, acc);
+    if (threadIdx.x == 0)
+        for (int q = 0; q < 3; ++q) a.out[q] = sh[q][0];
+    return true;
+}
+
+__device__ __forceinline__ void reduce_mass(const ReduceArgs& a, float* lds) {
+    const uint32_t P = a.runs[0].P;
+    const int64_t n = *a.n_cells;
+    if (a.runs[0].n_slots == 0) return;
+    const float* const gw = a.pp + 3 * a.cap;
+    const int64_t block = blockIdx.x - a.nb, blocks = gridDim.x - a.nb;
+    if (P < kMassCols) {
+        for (int64_t i = block * kReduceThreads + threadIdx.x; i < n; i += blocks * kReduceThreads) {
+            double s = 0.0;
+            for (uint32_t j = 0; j < P; ++j) s += (double)gw[(size_t)i * P + j];
+            a.dmass[a.cells[i]] = (float)(s / (double)P);
         }
+        return;
     }
-    for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] = acc[q];
-    __syncthreads();
-    for (int d = 128; d >= 1; d >>= 1) {
-        if ((int)threadIdx.x < d)
-            for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + d];
-        __syncthreads();
+    constexpr int kWaves = kReduceThreads / kWave, kPitch = kWave + 1;
+    const int lane = threadIdx.x & (kWave - 1);
+    float* const tile = lds + (threadIdx.x / kWave) * kMassRows * kPitch;
+    for (int64_t i0 = (block * kWaves + threadIdx.x / kWave) * kMassRows; i0 < n; i0 += blocks * kWaves * kMassRows) {
+        double s = 0.0;
+        for (uint32_t j0 = 0; j0 < P; j0 += kWave) {
+            const uint32_t cols = min(P - j0, (uint32_t)kWave);
+            float v[kMassRows];
+#pragma unroll
+            for (int r = 0; r < kMassRows; ++r)
+                v[r] = i0 + r < n && (uint32_t)lane < cols ? gw[(size_t)(i0 + r) * P + j0 + lane] : 0.0f;
+#pragma unroll
+            for (int r = 0; r < kMassRows; ++r) tile[r * kPitch + lane] = v[r];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");  // the tile is the wave's own
+            if (lane < kMassRows)
+                for (uint32_t j = 0; j < cols; ++j) s += (double)tile[lane * kPitch + j];
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        if (lane < kMassRows && i0 + lane < n) a.dmass[a.cells[i0 + lane]] = (float)(s / (double)P);
     }
-    if (threadIdx.x == 0)
-        for (int q = 0; q < 3; ++q) part[3 * (size_t)blockIdx.x + q] = sh[q][0];
 }
 
-__global__ __launch_bounds__(256) void k_reduce_final(const double* __restrict__ part, int nb, double* __restrict__ out) {
-    __shared__ double sh[3][256];
-    double acc[3] = {0.0, 0.0, 0.0};
-    for (int b = threadIdx.x; b < nb; b += 256)
-        for (int q = 0; q < 3; ++q) acc[q] += part[3 * (size_t)b + q];
-    for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] = acc[q];
-    __syncthreads();
-    for (int d = 128; d >= 1; d >>= 1) {
-        if ((int)threadIdx.x < d)
-            for (int q = 0; q < 3; ++q) sh[q][threadIdx.x] += sh[q][threadIdx.x + d];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0)
-        for (int q = 0; q < 3; ++q) out[q] = sh[q][0];
-}
-
-// dL/dmass of release cell i: (sum over its P particles of sum gD w, in order, binary64) / P
-__global__ __launch_bounds__(256) void k_dmass(const float* __restrict__ gw, const int32_t* __restrict__ cells,
-                                               const int32_t* __restrict__ n_cells, const RunConst* __restrict__ runs,
-                                               float* __restrict__ dmass) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (runs[0].n_slots == 0 || i >= (int64_t)*n_cells) return;
-    const uint32_t P = runs[0].P;
-    double s = 0.0;
-    for (uint32_t j = 0; j < P; ++j) s += (double)gw[(size_t)i * P + j];
-    dmass[cells[i]] = (float)(s / (double)P);
+__global__ __launch_bounds__(kReduceThreads) void k_smooth_reduce(ReduceArgs a) {
+    __shared__ union {
+        double sum[3][kReduceThreads];
+        float tile[kReduceThreads / kWave * kMassRows * (kWave + 1)];
+    } sh;
+    if (blockIdx.x < a.nb)
+        reduce_params(a, sh.sum);
+    else
+        reduce_mass(a, sh.tile);
 }
 
 // fixed point (2^-24) -> float, the deposit and (grid y = 1) the velocity raster; four values a thread, by 16-byte
@@ -768,13 +843,11 @@ hipError_t launch_smooth_backward_kernel(const SmoothArgs& a, int variant, hipSt
     return hipGetLastError();
 }
 
-hipError_t launch_smooth_reductions(const SmoothArgs& a, const int32_t* n_cells, float* dmass, int64_t n_grid,
+hipError_t launch_smooth_reductions(const SmoothArgs& a, const int32_t* n_cells, float* dmass, int64_t max_cells,
                                     double* part, double* dparams, hipStream_t s) {
-    const int nb = (int)smooth_reduce_blocks(a.cap);
-    hipLaunchKernelGGL(k_reduce_params, dim3(nb), dim3(256), 0, s, a.pp, a.cap, a.runs, part);
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(256), 0, s, part, nb, dparams);
-    const unsigned blocks = (unsigned)((n_grid + 255) / 256);
-    if (blocks) hipLaunchKernelGGL(k_dmass, dim3(blocks), dim3(256), 0, s, a.pp + 3 * a.cap, a.cells, n_cells, a.runs, dmass);
+    ReduceArgs r{a.pp, a.cap, a.runs, part, dparams, a.queues, (uint32_t)smooth_reduce_blocks(a.cap), a.cells, n_cells, dmass};
+    const int64_t mass = std::min<int64_t>((max_cells + 63) / 64, 4096);  // 16 cells a wave, then the next ones
+    hipLaunchKernelGGL(k_smooth_reduce, dim3(r.nb + (uint32_t)mass), dim3(kReduceThreads), 0, s, r);
     return hipGetLastError();
 }
 
