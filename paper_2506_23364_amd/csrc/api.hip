@@ -1032,10 +1032,27 @@ avl::SmoothArgs smooth_args(const float* dem, const float* mass, int32_t H, int3
 }  // namespace
 
 namespace {
+avl::SetupOne setup_of(const avl::SmoothWs& sw, const avl_params& p, float cell_size, uint32_t P, uint64_t seed,
+                       uint32_t run_id, int64_t cap_cells, int32_t* status, const avl_params* p_dev,
+                       const avl::RunSpec* spec_dev) {
+    avl::SetupOne su{};
+    su.spec_dev = p_dev ? spec_dev : nullptr;
+    su.p_dev = p_dev;
+    su.spec = {0u, 0u, 0u, run_id, (unsigned long long)seed};
+    su.p = p;
+    su.cs = cell_size;
+    su.P = P;
+    su.run = sw.w.runs;
+    su.run_off = sw.w.run_off;
+    su.status = status;
+    su.cap_cells = cap_cells;
+    return su;
+}
+
 // The smooth forward pass. `prepared`: the workspace already holds this mask's release cells, padded DEM,
 // start records and per-particle masses from an earlier pass with the same DEM, mask, mass and particles per
-// cell (a calibration loop, where only the friction parameters change between passes), so only the run
-// constants are set up again. `p_dev`, `spec_dev` (nullable, together): the run constants are set up from
+// cell (a calibration loop, where only the friction parameters change between passes), and the run constants, cleared
+// rasters, counters and queues from the end of that loop's previous iteration. `p_dev`, `spec_dev` (nullable, together): the run constants are set up from
 // these device copies of the parameters and the run (a loop that updates the parameters on the device);
 // `params` then serves only for the host checks of the parameters the loop does not change.
 int smooth_forward(const float* dem, const uint8_t* mask, const float* mass, int32_t H, int32_t W,
@@ -1068,22 +1085,9 @@ int smooth_forward(const float* dem, const uint8_t* mask, const float* mass, int
     clear.fill[2] = {reinterpret_cast<uint32_t*>(sw.w.queues), 2 * avl::kXcds * (int64_t)avl::kQueueStride, 0u};
     clear.fill[3] = {reinterpret_cast<uint32_t*>(a.stats), 8, 0u};
     auto zero = [&]() -> hipError_t { return avl::launch_prepare(clear, s); };
-    avl::SetupOne su{};
-    su.spec_dev = p_dev ? spec_dev : nullptr;
-    su.p_dev = p_dev;
-    su.spec = {0u, 0u, 0u, run_id, (unsigned long long)seed};
-    su.p = *params;
-    su.cs = cell_size;
-    su.P = particles_per_cell;
-    su.run = sw.w.runs;
-    su.run_off = sw.w.run_off;
-    su.status = status;
-    su.cap_cells = max_release_cells;
-    if (prepared) {
-        if ((e = avl::launch_setup_one(su, H, W, sw.w.n_cells, s)) != hipSuccess)
-            return hip_fail(e, "avl_trajectories_smooth: run setup");
-        if ((e = zero()) != hipSuccess) return hip_fail(e, "avl_trajectories_smooth: zero");
-    } else {
+    const avl::SetupOne su = setup_of(sw, *params, cell_size, particles_per_cell, seed, run_id, max_release_cells, status,
+                                      p_dev, spec_dev);
+    if (!prepared) {
         avl::PrepArgs pa = clear;
         pa.dem = dem;
         pa.dem_pad = sw.dem_pad;
@@ -1139,18 +1143,20 @@ int avl_trajectories_smooth(const float* dem, const uint8_t* mask, const float* 
 }
 
 namespace {
-// The adjoint of the pass smooth_forward left in the workspace; p_dev (nullable): xi is read from this device
-// copy of the parameters (the loop that keeps them on the device).
+// The adjoint of the pass smooth_forward left in the workspace; step (nullable): an iteration of the calibration loop, which
+// has cleared the queues already, reads xi from the device copy of the parameters and takes this step in place of writing
+// dL/dparams and dL/dmass (then null).
 int smooth_backward(const float* dem, const uint8_t* mask, const float* mass, int32_t H, int32_t W,
                     float cell_size, const avl_params* params, uint32_t particles_per_cell,
                     uint32_t step_limit, int32_t max_release_cells,
                     const float* grad_deposit, double* dparams, float* dmass, float* per_particle,
-                    void* workspace, size_t workspace_bytes, void* stream, const avl_params* p_dev) {
+                    void* workspace, size_t workspace_bytes, void* stream, const avl::CalibStep* step) {
     g_last_error.clear();
     int rc = smooth_checks("avl_trajectories_backward", dem, mask, H, W, cell_size, params, particles_per_cell,
                            step_limit, max_release_cells, workspace, workspace_bytes);
     if (rc != AVL_OK) return rc;
-    if (!grad_deposit || !dparams || !dmass) return fail(AVL_EINVAL, "avl_trajectories_backward: null pointer");
+    if (!grad_deposit || (!step && (!dparams || !dmass)))
+        return fail(AVL_EINVAL, "avl_trajectories_backward: null pointer");
     const int64_t n = (int64_t)H * W;
     hipStream_t s = static_cast<hipStream_t>(stream);
     avl::SmoothWs sw;
@@ -1158,10 +1164,10 @@ int smooth_backward(const float* dem, const uint8_t* mask, const float* mass, in
     avl::SmoothArgs a = smooth_args(dem, mass, H, W, cell_size, params, particles_per_cell, step_limit,
                                     max_release_cells, sw);
     a.gD = grad_deposit;
-    a.pdev = p_dev;
+    a.pdev = step ? step->p : nullptr;
     hipError_t e;
     avl::PrepArgs clear{};
-    clear.fill[0] = {reinterpret_cast<uint32_t*>(dmass), n, 0u};
+    if (dmass) clear.fill[0] = {reinterpret_cast<uint32_t*>(dmass), n, 0u};
     clear.fill[1] = {reinterpret_cast<uint32_t*>(sw.w.queues), 2 * avl::kXcds * (int64_t)avl::kQueueStride, 0u};
     auto zero = [&]() -> hipError_t { return avl::launch_prepare(clear, s); };
     int variant = 0;
@@ -1171,9 +1177,10 @@ int smooth_backward(const float* dem, const uint8_t* mask, const float* mass, in
                            [&](int v) { return avl::launch_smooth_backward_kernel(a, v, s); }, &variant, &tuned)) !=
         hipSuccess)
         return hip_fail(e, "avl_trajectories_backward: autotune");
-    if ((e = zero()) != hipSuccess) return hip_fail(e, "avl_trajectories_backward: zero");
+    if ((!step || tuned) && (e = zero()) != hipSuccess) return hip_fail(e, "avl_trajectories_backward: zero");
     if ((e = avl::launch_smooth_backward_kernel(a, variant, s)) != hipSuccess ||
-        (e = avl::launch_smooth_reductions(a, sw.w.n_cells, dmass, max_release_cells, sw.part, dparams, s)) !=
+        (e = step ? avl::launch_calib_step(a, sw.part, *step, s)
+                  : avl::launch_smooth_reductions(a, sw.w.n_cells, dmass, max_release_cells, sw.part, dparams, s)) !=
             hipSuccess)
         return hip_fail(e, "avl_trajectories_backward: launch");
     if (per_particle && a.cap &&
@@ -1367,11 +1374,8 @@ struct CalibWs {
     char* smooth;      // the smooth pass's own workspace (checkpoints for the adjoint)
     size_t smooth_bytes;
     int64_t* dep_q;    // H*W
-    float* dep;        // H*W
     float* gD;         // H*W
-    float* dmass;      // H*W
     double* part;      // loss partial sums
-    double* scal;      // [loss, dL/dmu, dL/dxi, dL/dh]
     int32_t* status;   // smooth pass status
     avl::RunSpec* spec;  // the run, on the device
     avl_params* p;       // the current parameters, on the device
@@ -1391,11 +1395,9 @@ size_t calib_layout(int32_t H, int32_t W, int32_t max_cells, uint32_t P, uint32_
         return p;
     };
     char* dq = take((size_t)n * 8);
-    char* d = take((size_t)n * 4);
     char* g = take((size_t)n * 4);
-    char* dm = take((size_t)n * 4);
     char* pt = take(avl::mse_partials() * sizeof(double));
-    char* sc = take(4 * sizeof(double) + sizeof(int32_t));
+    char* sc = take(sizeof(int32_t));
     char* spc = take(sizeof(avl::RunSpec));
     char* pp = take(sizeof(avl_params));
     char* stt = take(avl::kCalibState * sizeof(double));
@@ -1405,12 +1407,9 @@ size_t calib_layout(int32_t H, int32_t W, int32_t max_cells, uint32_t P, uint32_
         c->smooth = base;
         c->smooth_bytes = sm;
         c->dep_q = reinterpret_cast<int64_t*>(dq);
-        c->dep = reinterpret_cast<float*>(d);
         c->gD = reinterpret_cast<float*>(g);
-        c->dmass = reinterpret_cast<float*>(dm);
         c->part = reinterpret_cast<double*>(pt);
-        c->scal = reinterpret_cast<double*>(sc);
-        c->status = reinterpret_cast<int32_t*>(sc + 4 * sizeof(double));
+        c->status = reinterpret_cast<int32_t*>(sc);
         c->spec = reinterpret_cast<avl::RunSpec*>(spc);
         c->p = reinterpret_cast<avl_params*>(pp);
         c->state = reinterpret_cast<double*>(stt);
@@ -1477,22 +1476,35 @@ int avl_calibrate(const float* dem, const uint8_t* mask, const float* mass, int3
         (void)hipStreamSynchronize(s);
         return code;
     };
+    avl::SmoothWs sw;
+    avl::smooth_layout(H, W, max_release_cells, particles_per_cell, step_limit, c.smooth, &sw);
+    avl::CalibStep step{};
+    step.loss_part = c.part;
+    step.n = (double)n;
+    step.state = c.state;
+    step.p = c.p;
+    step.c = ac;
+    step.err = c.err;
+    step.next = setup_of(sw, *start, cell_size, particles_per_cell, seed, run_id, max_release_cells, c.status, c.p, c.spec);
+    step.n_cells = sw.w.n_cells;
+    step.stats = sw.w.stats;
+    unsigned long long* const dep_q = reinterpret_cast<unsigned long long*>(c.dep_q);
     for (int32_t t = 0; t < n_iters; ++t) {
-        // after the first pass the release cells, padded DEM, start records and masses are in the workspace
+        // after the first pass the release cells, padded DEM, start records and masses are in the workspace, and each
+        // kernel leaves what the next ones need cleared and set up
         if ((rc = smooth_forward(dem, mask, mass, H, W, cell_size, start, particles_per_cell, step_limit, seed,
-                                 run_id, max_release_cells, 0u, c.dep_q, c.dep, nullptr, nullptr, nullptr, c.status,
+                                 run_id, max_release_cells, 0u, c.dep_q, nullptr, nullptr, nullptr, nullptr, c.status,
                                  c.smooth, c.smooth_bytes, stream, t > 0, c.p, c.spec)) != AVL_OK)
             return drained(rc);
-        if ((e = avl::launch_mse_grad(c.dep, target, n, cgrad, c.gD, c.part, c.scal, s)) != hipSuccess)
+        if ((e = avl::launch_calib_loss(dep_q, target, n, cgrad, c.gD, c.part, sw.w.queues, s)) != hipSuccess)
             return drained(hip_fail(e, "avl_calibrate: loss"));
-        if ((rc = smooth_backward(dem, mask, mass, H, W, cell_size, start, particles_per_cell, step_limit,
-                                  max_release_cells, c.gD, c.scal + 1, c.dmass, nullptr, c.smooth, c.smooth_bytes,
-                                  stream, c.p)) != AVL_OK)
-            return drained(rc);
         const int32_t slot = t % kCalibRows;
-        if ((e = avl::launch_adam_step(c.scal, c.status, c.state, c.p, c.hist + 5 * slot, ac, t, c.err, s)) !=
-            hipSuccess)
-            return drained(hip_fail(e, "avl_calibrate: step"));
+        step.row = c.hist + 5 * slot;
+        step.t = t;
+        if ((rc = smooth_backward(dem, mask, mass, H, W, cell_size, start, particles_per_cell, step_limit,
+                                  max_release_cells, c.gD, nullptr, nullptr, nullptr, c.smooth, c.smooth_bytes,
+                                  stream, &step)) != AVL_OK)
+            return drained(rc);
         if (slot == kCalibRows - 1 || t == n_iters - 1) {
             // stream-ordered before the next step overwrites the rows
             if ((e = hipMemcpyAsync(history + 5 * (int64_t)(t - slot), c.hist, (size_t)(slot + 1) * 5 * sizeof(double),

@@ -209,7 +209,6 @@ struct SetupOne {
     int32_t* status;              // nullable
     int64_t cap_cells;
 };
-hipError_t launch_setup_one(const SetupOne& u, int H, int W, const int32_t* n_cells, hipStream_t s);
 // Per mask the row-major list of its nonzero texels behind launch_prepare's counts, and their number into n_cells. With
 // starts (one mask): the start record of each of the first cap, with mpc also the mass each of its particles carries
 // (mass null: 1 per texel). With setup.run: the single run's table.
@@ -305,10 +304,7 @@ hipError_t launch_smooth_reductions(const SmoothArgs& a, const int32_t* n_cells,
 // q0 -> out0 and q1 -> out1 (either pair may be null)
 hipError_t launch_q_to_float(const unsigned long long* q0, float* out0, const unsigned long long* q1, float* out1, int64_t n,
                              hipStream_t s);
-// calibration loss: gD = c (D - T) and L = sum (D - T)^2 / N (binary64, fixed order) into *loss
-hipError_t launch_mse_grad(const float* dep, const float* target, int64_t n, float c, float* gD, double* part,
-                           double* loss, hipStream_t s);
-size_t mse_partials();
+size_t mse_partials();  // blocks of the calibration loss
 
 // Device side of the calibration loop. State: th_mu, th_xi, m_mu, m_xi, v_mu, v_xi, beta1^t, beta2^t (binary64).
 struct AdamConsts {
@@ -318,11 +314,29 @@ constexpr int kCalibState = 8;
 // writes the run spec, the parameters and the initial state (th = the start's mu, xi; m = v = 0; products 1)
 hipError_t launch_calib_init(RunSpec spec, ::avl_params start, RunSpec* spec_dev, ::avl_params* p_dev, double* state,
                              int32_t* err, hipStream_t s);
-// one Adam step from scal = [loss, dL/dmu, dL/dxi, dL/dh]: writes the history row (loss, mu, xi, dL/dmu, dL/dxi,
-// before the step), updates the state and the parameters; the first iteration whose pass reported a nonzero
-// status is kept in err = (status, iteration)
-hipError_t launch_adam_step(const double* scal, const int32_t* status, double* state, ::avl_params* p_dev,
-                            double* row, AdamConsts c, int32_t t, int32_t* err, hipStream_t s);
+// The loss between the two passes of an iteration: gD = c (D - T) with D from the deposit's fixed point, and the partial
+// sums of (D - T)^2 (binary64, fixed order). It leaves dep_q cleared for the next iteration's forward and the queues for
+// this one's adjoint.
+hipError_t launch_calib_loss(unsigned long long* dep_q, const float* target, int64_t n, float c, float* gD, double* part,
+                             unsigned long long* queues, hipStream_t s);
+// The end of an iteration: L from the partial sums, dL/dparams of the adjoint, one Adam step on them; writes the history row
+// (loss, mu, xi, dL/dmu, dL/dxi, before the step), updates the state and the parameters; the first iteration whose
+// pass reported a nonzero status is kept in err = (status, iteration). Then it clears the queues and the statistics and
+// sets up the next iteration's run.
+struct CalibStep {
+    const double* loss_part;
+    double n;
+    double* state;
+    ::avl_params* p;
+    double* row;
+    AdamConsts c;
+    int32_t t;
+    int32_t* err;
+    SetupOne next;  // its status is the pass's own until then
+    const int32_t* n_cells;
+    unsigned long long* stats;
+};
+hipError_t launch_calib_step(const SmoothArgs& a, double* part, const CalibStep& c, hipStream_t s);
 hipError_t launch_finalize_vmax(uint32_t* vmax_bits, int64_t n, hipStream_t s);
 
 // Persistent-grid shape of kernel variant `variant` on the current device; number of variants.

@@ -210,17 +210,6 @@ __global__ __launch_bounds__(1024) void k_scan_counts(uint32_t* __restrict__ blk
     if (threadIdx.x == 0) n_cells[blockIdx.x] = (int32_t)carry;
 }
 
-// ------------------------------------------------------------------------------------------ run constants
-
-__global__ void k_setup_one(SetupOne u, int32_t H, int32_t W, const int32_t* __restrict__ n_cells) {
-    setup_one(u, H, W, (int64_t)*n_cells);
-}
-
-hipError_t launch_setup_one(const SetupOne& u, int H, int W, const int32_t* n_cells, hipStream_t s) {
-    hipLaunchKernelGGL(k_setup_one, dim3(1), dim3(1), 0, s, u, H, W, n_cells);
-    return hipGetLastError();
-}
-
 // ------------------------------------------------------------------------------------------ cells and records
 
 // Block (chunk, mask): the chunk's release texels in order behind those of the chunks before it, and per texel its start
