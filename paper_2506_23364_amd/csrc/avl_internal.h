@@ -281,7 +281,8 @@ struct SmoothArgs {
     float g2, g2dl, xi, h;                  // 2g, 2g * dl (dl = step_cells * cell_size), xi, h
     const float* dem_pad;                   // the DEM with a replicated border, (H + 2) x (W + 2)
     uint32_t pad_bytes;                     // its bytes, < 2^32
-    uint32_t spl;                           // particle slots per lane of a small problem (set by the launchers)
+    uint32_t spl;                           // forward: particle slots per lane of a small problem (set by the launcher)
+    uint32_t window;                        // adjoint: particles a block sorts by path length (set by the launcher)
     const StartRec* starts;                 // per release cell: the start state of its particles
     const float* mpc;                       // per release cell: the mass of each of its particles
     DivU32 pdiv;                            // slot -> release cell (division by the particles per cell)

@@ -110,6 +110,17 @@ __device__ __forceinline__ void steer(float& dx, float& dy, float gx, float gy, 
     }
 }
 
+// inclusive sum over the wave's lanes
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) {
+    const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+    for (int d = 1; d < kWave; d <<= 1) {
+        uint32_t t = __shfl_up(v, d, kWave);
+        if (lane >= d) v += t;
+    }
+    return v;
+}
+
 // 24 random bits m -> 2 (m 2^-24) - 1, uniform in [-1, 1). Both products are exact and so is the difference
 // ((m - 2^23) 2^-23 needs at most 24 significant bits), so one fma gives the same bits.
 __device__ __forceinline__ float signed_unit(uint32_t u) {

@@ -27,16 +27,6 @@ static_assert(kPrepThreads == kScanThreads, "the counting role scans with the bl
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at a 4-byte aligned address
 }  // namespace
 
-__device__ inline uint32_t wave_incl_scan(uint32_t v) {
-    const int lane = threadIdx.x & (kWave - 1);
-#pragma unroll
-    for (int d = 1; d < kWave; d <<= 1) {
-        uint32_t t = __shfl_up(v, d, kWave);
-        if (lane >= d) v += t;
-    }
-    return v;
-}
-
 // exclusive scan of one value per thread over a block of kScanThreads; returns the block total in *total
 __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t* total) {
     __shared__ uint32_t wsum[kScanThreads / kWave];

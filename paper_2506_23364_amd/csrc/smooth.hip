@@ -28,8 +28,8 @@ using namespace dev;
 namespace {
 
 constexpr uint32_t kCkpt = 64;        // steps between checkpoints (even: segments start on even steps)
-constexpr int kSmoothBlock = 256;
-constexpr int kBackwardGrid = 1536;   // blocks of the adjoint kernel at most (its scratch is sized for this)
+constexpr int kBackwardBlock = 256, kBackwardGrid = 1536;  // the adjoint kernel (its scratch is sized for this)
+static_assert(kBackwardGrid % kXcds == 0, "each XCD has the same number of blocks");
 constexpr int kReduceChunk = 4096;    // particles per block of the gradient reduction
 static_assert(kCkpt % 2 == 0, "segments must start on even steps (one Philox block serves two steps)");
 
@@ -393,11 +393,39 @@ __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
     if (threadIdx.x < 4 && bst[threadIdx.x]) atomicAdd(a.stats + threadIdx.x, bst[threadIdx.x]);
 }
 
-__global__ __launch_bounds__(kSmoothBlock) void k_smooth_backward(SmoothArgs a) {
-    if ((uint64_t)blockIdx.x >= active_blocks(a.run_off[1], kSmoothBlock, a.spl)) return;  // small problems: fewer blocks
+// The adjoint takes as many steps forward and back as the particle took, which the forward has recorded. Of 64 consecutive
+// particles all lanes wait for the longest, 15 steps where the mean is 9 on a 1024^2 scene: so a block takes a window of
+// consecutive particles, sorts them by length in LDS (a counting sort), and its waves take 64 at a time, the longest
+// first. What is left is the chain of the longest paths, at some 0.8 us a step forward and back: the forward steps run in
+// pairs with the next pair's random words computed behind a gather, and a segment's first steps are kept in LDS.
+// Long paths lie together: where each block has one window, the windows are dealt out in scattered pieces of 64 particles,
+// so that each has its share of them; where blocks take several in turn, a window is consecutive, each XCD's blocks have
+// one stretch of the particles, for its L2, and blocks with long paths take fewer windows.
+// 640,000 particles of up to 78 steps: adjoint and its sums 205 -> 160 us (191 with consecutive windows). Larger blocks, wave
+// priorities for the long groups and more or fewer steps in LDS gave nothing or cost up to 15 %.
+constexpr int kLenBins = 128;
+constexpr uint32_t kMaxWindow = 2048;
+constexpr uint32_t kLdsSteps = 8;  // a lane's first (a_k, v^2_{k+1}) of a segment are in LDS, the rest in a.scratch
+
+__device__ __forceinline__ uint32_t length_bin(uint32_t rec) {
+    const uint32_t n = (rec & 3u) == kEndExit ? 0u : rec >> 2;
+    return n < 64u ? n : min(63u + n / 64u, (uint32_t)kLenBins - 1u);
+}
+
+__global__ __launch_bounds__(kBackwardBlock) void k_smooth_backward(SmoothArgs a) {
+    __shared__ uint16_t order[kMaxWindow];
+    __shared__ uint8_t len[kMaxWindow];
+    __shared__ uint32_t bins[kLenBins];
+    __shared__ uint32_t next_group, next_win, count;
+    __shared__ float2 near[kLdsSteps * kBackwardBlock];
     const int lane = threadIdx.x & (kWave - 1);
-    const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
     const RunConst rc = uniform_run(a.runs[0]);
+    const uint32_t windows = (uint32_t)((rc.n_slots + a.window - 1) / a.window);
+    const uint32_t per = (windows + kXcds - 1) / kXcds;  // windows of an XCD's stretch
+    const uint32_t each = gridDim.x / kXcds;             // blocks of an XCD, a window each to begin with
+    uint32_t part = blockIdx.x % kXcds;
+    uint32_t win = blockIdx.x / kXcds < per ? part * per + blockIdx.x / kXcds : windows;
+    if (win >= windows && per <= each) return;
     const int H = a.H, W = a.W;
     const PadDem dd = pad_dem(a);
     const size_t T = (size_t)gridDim.x * blockDim.x;
@@ -405,19 +433,8 @@ __global__ __launch_bounds__(kSmoothBlock) void k_smooth_backward(SmoothArgs a) 
     const size_t cplane = (size_t)a.C * a.cap;
     const float g2dl = a.g2dl;
     const float xi = a.pdev ? a.pdev->xi : a.xi;  // a device-side loop keeps the parameters on the device
-    Dispenser disp;
-    {
-        const uint64_t total = wave_bcast64(a.run_off[1]);
-        const uint64_t nb = min((uint64_t)gridDim.x, active_blocks(total, blockDim.x, a.spl));
-        const uint32_t wpb = blockDim.x / kWave;
-        disp.init(total, xcd_id(), (uint64_t)blockIdx.x * wpb + threadIdx.x / kWave, nb * wpb);
-    }
 
-    for (;;) {
-        const uint64_t idle = __ballot(true);
-        if (disp.drained()) break;
-        const uint64_t slot = disp.take(a.queues, idle, lane, below);
-        if (slot >= rc.n_slots) continue;
+    auto particle = [&](uint64_t slot) {
         uint32_t rep = 0;
         const uint64_t i = cell_of_slot(slot, a, rc.P, &rep);
         const StartRec st = a.starts[i];  // the release state, as the forward started the particle
@@ -431,7 +448,6 @@ __global__ __launch_bounds__(kSmoothBlock) void k_smooth_backward(SmoothArgs a) 
             State s{};
             int32_t c_last = -1;
             if (a.C > 0) c_last = (int32_t)min(n_end / kCkpt, a.C - 1);
-            uint32_t n0 = 0;
             auto load = [&](int32_t c) {
                 s.x0 = st.x;
                 s.y0 = st.y;
@@ -459,72 +475,87 @@ __global__ __launch_bounds__(kSmoothBlock) void k_smooth_backward(SmoothArgs a) 
                 s.gy = sm.gy;
             };
             load(c_last);
-            n0 = c_last < 0 ? 0u : (uint32_t)c_last * kCkpt;
-            // segments start at checkpoints, multiples of kCkpt (even): the step's parity is that of the trip
-            // count, the same for every lane still in the loop
+            const uint32_t n0 = c_last < 0 ? 0u : (uint32_t)c_last * kCkpt;
+            // Steps c0 .. c0 + m - 1 from s, m <= kCkpt, in pairs, the next pair's words computed while the second
+            // step's patch is on its way. c0 is a checkpoint and so even: afterwards `words` are those of the pair
+            // that step c0 + m belongs to.
             uint4 words{};
-            for (uint32_t t = 0; n0 + t < n_end; ++t) {
-                if ((t & 1u) == 0u) words = step_words(n0 + t, rep, cell_id, rc);
-                const StepOut o = step(s, (t & 1u) ? words.z : words.x, (t & 1u) ? words.w : words.y, rc, dd, H, W, a.g2);
-                a.scratch[(size_t)t * T + gtid] = make_float2(o.a, s.v2);
-            }
+            auto recompute = [&](uint32_t c0, uint32_t m) {
+                auto keep = [&](uint32_t t, float aa) {
+                    if (t < kLdsSteps)
+                        near[t * kBackwardBlock + threadIdx.x] = make_float2(aa, s.v2);
+                    else
+                        a.scratch[(size_t)t * T + gtid] = make_float2(aa, s.v2);
+                };
+                words = step_words(c0, rep, cell_id, rc);
+                for (uint32_t t = 0; t < m; t += 2) {
+                    keep(t, step(s, words.x, words.y, rc, dd, H, W, a.g2).a);
+                    if (t + 1 >= m) break;
+                    const Target tg = step_begin(s, words.z, words.w, rc, dd);
+                    words = step_words(c0 + t + 2, rep, cell_id, rc);
+                    keep(t + 1, step_end(s, tg, rc, H, W, a.g2).a);
+                }
+            };
+            recompute(n0, n_end > n0 ? n_end - n0 : 0u);
             float px = s.x, py = s.y;
-            float lam = 0.0f, gt = 0.0f;
-            bool stop = false;
-            if (reason == kEndStop) {
-                const float xp = s.x, yp = s.y, v2p = s.v2;
-                if ((n_end & 1u) == 0u) words = step_words(n_end, rep, cell_id, rc);
+            float lam = 0.0f;
+            const bool stop = reason == kEndStop;
+            float sx = 0.0f, sy = 0.0f, v2p = 0.0f, num = 0.0f;
+            if (stop) {
+                const float xp = s.x, yp = s.y;
+                v2p = s.v2;
                 const StepOut o = step(s, (n_end & 1u) ? words.z : words.x, (n_end & 1u) ? words.w : words.y, rc, dd, H, W, a.g2);
-                const float t = v2p > 0.0f ? v2p / (v2p - o.num) : 0.0f;
-                px = xp + t * (o.x1 - xp);
-                py = yp + t * (o.y1 - yp);
-                // dL/dp* through the splat weights, dL/dt*
-                const Corners k = corners(H, W, px, py);
-                const float g00 = a.gD[(size_t)k.ra * W + k.ca], g01 = a.gD[(size_t)k.ra * W + k.cb];
-                const float g10 = a.gD[(size_t)k.rb * W + k.ca], g11 = a.gD[(size_t)k.rb * W + k.cb];
+                num = o.num;
+                const float t = v2p > 0.0f ? v2p / (v2p - num) : 0.0f;
+                sx = o.x1 - xp;
+                sy = o.y1 - yp;
+                px = xp + t * sx;
+                py = yp + t * sy;
+            }
+            // dL/dp* through the splat weights, dL/dt*
+            const Corners k = corners(H, W, px, py);
+            const float g00 = a.gD[(size_t)k.ra * W + k.ca], g01 = a.gD[(size_t)k.ra * W + k.cb];
+            const float g10 = a.gD[(size_t)k.rb * W + k.ca], g11 = a.gD[(size_t)k.rb * W + k.cb];
+            const float w00 = (1.0f - k.fx) * (1.0f - k.fy), w01 = k.fx * (1.0f - k.fy);
+            const float w10 = (1.0f - k.fx) * k.fy, w11 = k.fx * k.fy;
+            gw = ((g00 * w00) + (g01 * w01)) + ((g10 * w10) + (g11 * w11));
+            if (stop) {
                 const float gpx = ((g01 - g00) * (1.0f - k.fy)) + ((g11 - g10) * k.fy);
                 const float gpy = ((g10 - g00) * (1.0f - k.fx)) + ((g11 - g01) * k.fx);
-                const float w00 = (1.0f - k.fx) * (1.0f - k.fy), w01 = k.fx * (1.0f - k.fy);
-                const float w10 = (1.0f - k.fx) * k.fy, w11 = k.fx * k.fy;
-                gw = ((g00 * w00) + (g01 * w01)) + ((g10 * w10) + (g11 * w11));
-                gt = mp * ((gpx * (o.x1 - xp)) + (gpy * (o.y1 - yp)));
-                const float Dn = v2p - o.num;
+                const float gt = mp * ((gpx * sx) + (gpy * sy));
+                const float Dn = v2p - num;
                 if (Dn > 0.0f) {
                     lam = gt / Dn;
                     dmu = -((gt * (v2p / Dn)) * (g2dl / Dn));
                 }
-                stop = true;
-            } else {
-                const Corners k = corners(H, W, px, py);
-                const float g00 = a.gD[(size_t)k.ra * W + k.ca], g01 = a.gD[(size_t)k.ra * W + k.cb];
-                const float g10 = a.gD[(size_t)k.rb * W + k.ca], g11 = a.gD[(size_t)k.rb * W + k.cb];
-                const float w00 = (1.0f - k.fx) * (1.0f - k.fy), w01 = k.fx * (1.0f - k.fy);
-                const float w10 = (1.0f - k.fx) * k.fy, w11 = k.fx * k.fy;
-                gw = ((g00 * w00) + (g01 * w01)) + ((g10 * w10) + (g11 * w11));
-            }
-            if (stop) {
                 // reverse sweep: the last segment from the scratch, then earlier segments recomputed
                 // an energy stop needs a step, so step_limit >= 1 and checkpoint 0 exists: c_last >= 0
                 for (int32_t c = c_last; c >= 0; --c) {
                     const uint32_t c0 = (uint32_t)c * kCkpt;
-                    const uint32_t c1 = (c == c_last) ? n_end : c0 + kCkpt;
+                    uint32_t m = n_end - c0;
                     if (c != c_last) {
                         load(c);
-                        for (uint32_t t = 0; c0 + t < c1; ++t) {
-                            if ((t & 1u) == 0u) words = step_words(c0 + t, rep, cell_id, rc);
-                            const StepOut o = step(s, (t & 1u) ? words.z : words.x, (t & 1u) ? words.w : words.y, rc, dd, H, W, a.g2);
-                            a.scratch[(size_t)t * T + gtid] = make_float2(o.a, s.v2);
-                        }
+                        m = kCkpt;
+                        recompute(c0, m);
                     }
-                    for (uint32_t k = c1; k-- > c0;) {
-                        const float2 e = a.scratch[(size_t)(k - c0) * T + gtid];
+                    auto back = [&](const float2 e) {
                         const float aa = e.x, v2n = e.y;
                         const float op = 1.0f + aa;
                         dmu = dmu - lam * (g2dl / op);
                         dxi = dxi + lam * ((v2n * aa) / (xi * op));
                         dh = dh + lam * ((v2n * aa) / (a.h * op));
                         lam = lam / op;
+                    };
+                    if (m > kLdsSteps) {
+                        float2 e = a.scratch[(size_t)(m - 1u) * T + gtid];
+                        for (uint32_t t = m - 1u; t > kLdsSteps; --t) {
+                            const float2 f = a.scratch[(size_t)(t - 1u) * T + gtid];  // on its way during the divisions
+                            back(e);
+                            e = f;
+                        }
+                        back(e);
                     }
+                    for (uint32_t t = min(m, kLdsSteps); t-- > 0;) back(near[t * kBackwardBlock + threadIdx.x]);
                 }
             }
         }
@@ -532,6 +563,61 @@ __global__ __launch_bounds__(kSmoothBlock) void k_smooth_backward(SmoothArgs a) 
         a.pp[a.cap + slot] = dxi;
         a.pp[2 * a.cap + slot] = dh;
         a.pp[3 * a.cap + slot] = gw;
+    };
+
+    const bool spread = per <= each;  // a window a block
+    for (;;) {
+        if (win < windows) {
+            auto slot_of = [&](uint32_t k) {
+                return spread ? ((uint64_t)(k / kWave) * windows + win) * kWave + k % kWave : (uint64_t)win * a.window + k;
+            };
+            for (uint32_t k = threadIdx.x; k < kLenBins; k += kBackwardBlock) bins[k] = 0u;
+            if (threadIdx.x == 0) next_group = 0u;
+            __syncthreads();
+            for (uint32_t k = threadIdx.x; k < a.window; k += kBackwardBlock) {
+                const uint64_t slot = slot_of(k);
+                if (slot < rc.n_slots) {
+                    const uint32_t b = length_bin(a.end_rec[slot]);
+                    len[k] = (uint8_t)b;
+                    atomicAdd(&bins[b], 1u);
+                }
+            }
+            __syncthreads();
+            if (threadIdx.x < kWave) {  // where each length's particles begin, the longest first
+                const int hi = kLenBins - 1 - 2 * lane;
+                const uint32_t n0 = bins[hi], n1 = bins[hi - 1];
+                const uint32_t upto = wave_incl_scan(n0 + n1);
+                bins[hi] = upto - n0 - n1;
+                bins[hi - 1] = upto - n1;
+                if (lane == kWave - 1) count = upto;
+            }
+            __syncthreads();
+            for (uint32_t k = threadIdx.x; k < a.window; k += kBackwardBlock)
+                if (slot_of(k) < rc.n_slots) order[atomicAdd(&bins[len[k]], 1u)] = (uint16_t)k;
+            __syncthreads();
+            for (;;) {
+                uint32_t g = 0;
+                if (lane == 0) g = atomicAdd(&next_group, 1u);
+                g = __builtin_amdgcn_readfirstlane(g) * kWave;
+                if (g >= count) break;
+                if (g + lane < count) particle(slot_of(order[g + lane]));
+            }
+        }
+        if (per <= each) break;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            next_win = windows;
+            for (int k = 0; k < kXcds; ++k, part = (part + 1) % kXcds) {
+                const uint32_t at = each + (uint32_t)atomicAdd(a.queues + part * kQueueStride, 1ull);
+                if (at < per && part * per + at < windows) {
+                    next_win = part * per + at;
+                    break;
+                }
+            }
+        }
+        __syncthreads();
+        win = next_win;
+        if (win >= windows) break;
     }
 }
 
@@ -807,7 +893,7 @@ hipError_t launch_calib_init(RunSpec spec, ::avl_params start, RunSpec* spec_dev
 // ------------------------------------------------------------------------------------------ launchers
 
 size_t smooth_checkpoints(uint32_t S) { return S == 0 ? 0 : (S + kCkpt - 1) / kCkpt; }
-size_t smooth_scratch_bytes() { return (size_t)kCkpt * kBackwardGrid * kSmoothBlock * sizeof(float2); }
+size_t smooth_scratch_bytes() { return (size_t)kCkpt * kBackwardGrid * kBackwardBlock * sizeof(float2); }
 size_t smooth_reduce_blocks(unsigned long long cap) { return (size_t)((cap + kReduceChunk - 1) / kReduceChunk) + 1; }
 
 namespace {
@@ -817,9 +903,10 @@ struct SmoothVariant {
     uint32_t spl;
 };
 // forward candidates: (threads per block, slots per lane), small blocks with a slot per lane for problems that leave SIMDs idle
-// otherwise (96,000 particles: 52 us with 1024 threads or two slots, 47 so); backward: slots per lane at 256 threads
+// otherwise (96,000 particles: 52 us with 1024 threads or two slots, 47 so)
 constexpr SmoothVariant kFwdVariants[] = {{256, 8}, {1024, 2}, {512, 2}, {1024, 1}, {256, 1}, {512, 1}};
-constexpr uint32_t kBwdSpl[] = {8, 2, 1, 4};
+// adjoint candidates: particles of a window
+constexpr uint32_t kBwdWindows[] = {1024, 512, 256, 2048};
 
 template <int kBlk, bool kVel>
 void launch_fwd(const SmoothArgs& a, hipStream_t s) {
@@ -837,7 +924,7 @@ void launch_fwd(const SmoothArgs& a, hipStream_t s) {
 }  // namespace
 
 int smooth_forward_variants() { return (int)(sizeof(kFwdVariants) / sizeof(kFwdVariants[0])); }
-int smooth_backward_variants() { return (int)(sizeof(kBwdSpl) / sizeof(kBwdSpl[0])); }
+int smooth_backward_variants() { return (int)(sizeof(kBwdWindows) / sizeof(kBwdWindows[0])); }
 
 hipError_t launch_smooth_forward(const SmoothArgs& a, int variant, hipStream_t s) {
     if (variant < 0 || variant >= smooth_forward_variants()) variant = 0;
@@ -854,8 +941,8 @@ hipError_t launch_smooth_forward(const SmoothArgs& a, int variant, hipStream_t s
 hipError_t launch_smooth_backward_kernel(const SmoothArgs& a, int variant, hipStream_t s) {
     if (variant < 0 || variant >= smooth_backward_variants()) variant = 0;
     SmoothArgs b = a;
-    b.spl = kBwdSpl[variant];
-    hipLaunchKernelGGL(k_smooth_backward, dim3(kBackwardGrid), dim3(kSmoothBlock), 0, s, b);
+    b.window = kBwdWindows[variant];
+    hipLaunchKernelGGL(k_smooth_backward, dim3(kBackwardGrid), dim3(kBackwardBlock), 0, s, b);
     return hipGetLastError();
 }
 

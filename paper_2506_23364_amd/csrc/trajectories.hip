@@ -45,11 +45,6 @@ namespace {
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
 using dev::kChunk;
 
-// LDS table accesses are relaxed atomics: lanes of the wave update slots concurrently.
-__device__ __forceinline__ uint32_t lds_ld(uint32_t* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-}
-
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 // four consecutive words of a table in LDS, 16-byte aligned, in one read

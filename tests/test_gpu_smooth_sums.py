@@ -39,3 +39,30 @@ def test_sums_in_order(avl, n_cells, P):
         # any order of n binary64 additions is within n ulps of the sum of magnitudes
         for k in range(3):
             assert abs(dp[k] - pp[k].sum()) <= 2.0 * n * 2.0 ** -53 * np.abs(pp[k]).sum()
+
+
+@pytest.mark.parametrize("n_cells,P,limit", [(1, 1, 500), (3, 85, 500), (1, 257, 500), (2, 1025, 500), (300, 7, 64), (300, 7, 65),
+                                             (200, 10, 3), (200, 10, 0),
+                                             (3100, 260, 3)])
+def test_adjoint_windows(avl, n_cells, P, limit):
+    """Every window size gives the oracle's terms: particles around a window's and a wave's, paths that end at the release, in
+    the first segment, at a checkpoint and segments later, more or fewer steps than are kept in LDS, exits and limits;
+    one window a block and (806,000 particles) several."""
+    import oracle
+    dem = synth.incline_fillet_dem(160, 10.0, seed=6)
+    mask = np.zeros(dem.shape, np.uint8)
+    mask.reshape(-1)[np.random.default_rng(P).permutation(dem.size // 2)[:n_cells]] = 1
+    rng = np.random.default_rng(n_cells)
+    gD = rng.standard_normal(dem.shape).astype(np.float32)
+    p = dict(synth.DEFAULT_PARAMS, mu=0.25, xi=1500.0, randomness=0.3)
+    want = oracle.smooth_backward(dem, mask, 10.0, oracle.make_params(**p), P, limit, 3, gD).per_particle
+    d, m, g = (torch.from_numpy(x).cuda() for x in (dem, mask, gD))
+    par = avl.Params.make(**p)
+    try:
+        for v in range(avl.smooth_tuning_variants()[1]):
+            avl.set_smooth_tuning(-1, v)
+            r = avl.trajectories_smooth(d, m, 10.0, par, P, limit, 3)
+            pp = avl.trajectories_backward(r, d, m, 10.0, par, P, limit, 3, g, per_particle=True)[2].cpu().numpy()
+            assert np.array_equal(pp[:, :n_cells * P].T, want), f"variant {v}"
+    finally:
+        avl.set_smooth_tuning(-1, -1)
