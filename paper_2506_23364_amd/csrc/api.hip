@@ -1294,8 +1294,7 @@ int avl_trajectories_batched(const float* dems, int32_t n_tiles, const uint8_t* 
     auto body = [&](const avl::LaunchShape& shape) -> hipError_t {
         hipError_t e;
         if ((e = prologue()) != hipSuccess) return e;
-        if ((e = timed_launch(a, true, shape, s)) != hipSuccess) return e;
-        return avl::launch_finalize_vmax(a.vmax2, raster, s);
+        return timed_launch(a, true, shape, s);
     };
 
     // the variant is chosen eagerly, before any capture (tuning runs need the run table in place)

@@ -110,8 +110,8 @@ struct TrajArgs {
     const unsigned long long* __restrict__ run_off;  // n_runs + 1 slot offsets, each a multiple of 64
     unsigned long long* __restrict__ queues;     // kXcds slot counters kQueueStride words apart, zero at launch
     uint32_t* __restrict__ counts;               // count rasters, zero at launch
-    uint32_t* __restrict__ vmax2;                // binary32 bits of the per-cell max of v^2 (v^2 >= 0, so bit
-                                                 // order is value order), zero at launch
+    uint32_t* __restrict__ vmax2;                // binary32 bits of the per-cell max of v^2, in a batch of v (both
+                                                 // >= 0, so bit order is value order), zero at launch
     unsigned long long* __restrict__ stats;      // 4 u64 per run: steps, exits, stops, step-limit ends
     int32_t H, W;
     uint32_t n_runs;

@@ -30,7 +30,8 @@
 //  - The slot range is split into one partition per XCD; windows and chunks come from the XCD's own
 //    partition first and from the others only when it is empty. Each XCD's L2 then holds its own band
 //    of the DEM (or its own runs).
-//  - Every run writes the caller's rasters directly (v^2 bits, turned into speeds by a finalize pass).
+//  - Every run writes the caller's rasters directly (a single run v^2 bits, turned into speeds by a finalize pass, a
+//    batch's runs the speeds).
 //    Per-XCD private copies bought nothing once the table had cut the atomics: the atomics are
 //    performed at the memory side either way, and zeroing and merging the copies cost 9 % at 8192^2.
 //  - Accumulation is integer only (u32 add; u32 max on the bits of v^2 >= 0, whose order is the value
@@ -44,6 +45,16 @@ namespace {
 
 constexpr uint32_t kEmpty = 0xFFFFFFFFu;
 using dev::kChunk;
+
+// Bits of sqrt(v^2), for the flush of a batch: the correctly rounded root is monotone, so the largest root is the root of
+// the largest v^2. A pass over the rasters that takes the root at the end reads and writes 8 bytes a texel for every run
+// (256 runs of 1024^2: 222 of 2560 us); a single run has few texels for its steps, and there the pass is the cheaper one
+// (8192^2 and 1.2e9 steps: 62 us of 8 ms, against 2 % of the kernel).
+__device__ __forceinline__ uint32_t root_bits(uint32_t v2) {
+    const bool odd = v2 != 0u && v2 - dev::kRootLo > 0x7F7FFFFFu - dev::kRootLo;
+    if (__builtin_expect(__ballot(odd) != 0ull, 0)) return __float_as_uint(sqrtf(__uint_as_float(v2)));
+    return v2 ? __float_as_uint(dev::sqrt_est(__uint_as_float(v2)).s) : 0u;
+}
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -239,7 +250,7 @@ void k_trajectories(TrajArgs a) {
                     sl = claim_slow(leave_key);
                     if (sl < 0) {
                         atomicAdd(counts + leave_key, 1u);
-                        if (leave_bits) global_max(vmax2 + leave_key, leave_bits);
+                        if (leave_bits) global_max(vmax2 + leave_key, kBatch ? root_bits(leave_bits) : leave_bits);
                     }
                 }
             }
@@ -685,6 +696,7 @@ void k_trajectories(TrajArgs a) {
                 tb.cnt[k] = fc[j] | (fc[j] << 16);
             } else if (ft[j] != kEmpty) {
                 if (fc[j]) atomicAdd(counts + ft[j], fc[j]);
+                if constexpr (kBatch) fv[j] = root_bits(fv[j]);
                 tb.tag[k] = kEmpty;
                 tb.cnt[k] = 0u;
                 tb.vmx[k] = 0u;
