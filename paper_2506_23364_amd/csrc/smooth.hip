@@ -213,6 +213,18 @@ __device__ __forceinline__ void splat(SumTable<kSlots>& tb, unsigned long long* 
     sum_add(tb, q, c11, a11, t11, splat_fixed(val * w11, small));
 }
 
+// the same splat straight to the raster
+__device__ __forceinline__ void splat_direct(unsigned long long* __restrict__ q, int H, int W, float x, float y, float val) {
+    const Corners k = corners(H, W, x, y);
+    const float w00 = (1.0f - k.fx) * (1.0f - k.fy), w01 = k.fx * (1.0f - k.fy);
+    const float w10 = (1.0f - k.fx) * k.fy, w11 = k.fx * k.fy;
+    const bool small = __ballot(!(fabsf(val) < 127.0f)) == 0ull;
+    atomicAdd(q + (uint32_t)(k.ra * W + k.ca), splat_fixed(val * w00, small));
+    atomicAdd(q + (uint32_t)(k.ra * W + k.cb), splat_fixed(val * w01, small));
+    atomicAdd(q + (uint32_t)(k.rb * W + k.ca), splat_fixed(val * w10, small));
+    atomicAdd(q + (uint32_t)(k.rb * W + k.cb), splat_fixed(val * w11, small));
+}
+
 // release cell of particle slot `slot`, and the particle's replica index within it
 __device__ __forceinline__ uint64_t cell_of_slot(uint64_t slot, const SmoothArgs& a, uint32_t P, uint32_t* rep) {
     const uint64_t i = (slot >> 32) == 0 ? (uint64_t)udiv((uint32_t)slot, a.pdiv) : slot / P;
@@ -224,7 +236,17 @@ __device__ __forceinline__ uint64_t cell_of_slot(uint64_t slot, const SmoothArgs
 
 // kBlk threads per block share the tables; a.spl particle slots per lane size the grid of a small problem. With kVel every
 // accepted step also splats the velocity raster, through a table that the block flushes every kVelPairs pairs of steps.
+// Few particles stay below the rate of the memory side's adds, which nothing waits for, while the table's round trips and
+// barriers lengthen each step; and the fewer particles share a release cell, the fewer splats the table can merge. So up to
+// kDirectSlots particles, or 2 kDirectSlots at eight a cell and with the square of their number up to 128 kDirectSlots at
+// one, the velocity goes straight to the raster. Short paths, direct against table: 2470 particles of 10 a cell 63 against
+// 76 us, 6000 of 10 69/80, 12,000 of 40 115/75; 80,000 of 1 203/304, 80,000 of 4 204/246, 320,000 of 4 555/361. Long paths:
+// 1600 of 8 183/199, 6000 of 10 263/207, 12,000 of 40 489/200, 12,000 of 4 254/267, 10,000 of 1 232/386.
 constexpr int kVelPairs = 16;
+constexpr unsigned long long kDirectSlots = 3072;
+__device__ __forceinline__ bool velocity_direct(unsigned long long slots, uint32_t P) {
+    return slots <= kDirectSlots || (P <= 8u && slots * P * P <= 128u * kDirectSlots);
+}
 template <int kBlk, bool kVel>
 __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
     if ((uint64_t)blockIdx.x >= active_blocks(a.run_off[1], kBlk, a.spl)) return;  // small problems: fewer blocks
@@ -256,6 +278,7 @@ __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
         }
     }
     __syncthreads();
+    const bool direct = kVel && velocity_direct(rc.n_slots, rc.P);
 
     bool alive = false;
     State s{};
@@ -317,7 +340,13 @@ __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
         }
         n += acc ? 1u : 0u;
         if constexpr (kVel) {
-            if (acc) splat(vel, a.vel_q, H, W, s.x, s.y, mp * sqrtf(s.v2));
+            if (acc) {
+                const float v = mp * sqrtf(s.v2);
+                if (direct)
+                    splat_direct(a.vel_q, H, W, s.x, s.y, v);
+                else
+                    splat(vel, a.vel_q, H, W, s.x, s.y, v);
+            }
         }
         alive = acc;
     };
@@ -326,7 +355,7 @@ __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
     // particle starts from its release cell's start record (one load, the mass per particle beside it).
     for (;;) {
         bool finished = false;
-        for (int pair = 0; !kVel || pair < kVelPairs; ++pair) {
+        for (int pair = 0; !kVel || direct || pair < kVelPairs; ++pair) {
             const uint64_t idle = __ballot(!alive);
             const bool drained = disp.drained();
             if (__popcll(idle) == kWave && drained) {
@@ -361,7 +390,7 @@ __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
             advance(o.x, o.y, true);
             advance(o.z, o.w, false);
         }
-        if constexpr (!kVel) break;
+        if (!kVel || direct) break;
         __syncthreads();
         for (int k = threadIdx.x; k < kVelSlots; k += kBlk) {
             if (vel.tag[k] != kDepEmpty) {
@@ -902,9 +931,10 @@ struct SmoothVariant {
     int block;
     uint32_t spl;
 };
-// forward candidates: (threads per block, slots per lane), small blocks with a slot per lane for problems that leave SIMDs idle
-// otherwise (96,000 particles: 52 us with 1024 threads or two slots, 47 so)
-constexpr SmoothVariant kFwdVariants[] = {{256, 8}, {1024, 2}, {512, 2}, {1024, 1}, {256, 1}, {512, 1}};
+// Forward candidates: (threads per block, slots per lane). Small blocks with a slot per lane serve problems that leave SIMDs
+// idle otherwise (96,000 particles: 52 us with 1024 threads or two slots, 47 so). The first is kept unless another is
+// faster, and holds for the larger problems of its size class too, since it leaves no lane a second round.
+constexpr SmoothVariant kFwdVariants[] = {{256, 1}, {1024, 2}, {512, 2}, {1024, 1}, {256, 8}, {512, 1}};
 // adjoint candidates: particles of a window
 constexpr uint32_t kBwdWindows[] = {1024, 512, 256, 2048};
 

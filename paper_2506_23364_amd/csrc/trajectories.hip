@@ -6,8 +6,9 @@
 //
 // Design for gfx950 (measured choices; the alternatives are recorded in the design notes):
 //  - One persistent grid sized to the chip's occupancy; one lane carries one particle at a time and its
-//    whole state stays in VGPRs. A lane whose particle ended takes the next particle slot in the same
-//    iteration, from a per-wave reservoir refilled 64 slots at a time.
+//    whole state stays in VGPRs. A lane whose particle ended takes the next particle slot before the next
+//    pair of steps: a single run's waves take exactly what their idle lanes need from the block's window, a
+//    batch's from a per-wave reservoir refilled 64 slots at a time (a chunk belongs to one run).
 //  - Slots are ordered replica-major within a release cell and run-major across runs; every run starts
 //    at a multiple of 64, so a 64-slot chunk belongs to one run. Release cells are in row-major order,
 //    so consecutive slots start at the same or neighbouring cells and their paths share most cells.
@@ -26,14 +27,14 @@
 //    boundaries), so the table sees the paths of neighbouring release cells together. Top-ups are guided:
 //    up to kWindow x kBlock slots, but at most half the partition's remainder over the blocks of an XCD,
 //    so windows shrink as the queues drain and the blocks finish together. A wave that runs the window
-//    dry mid-epoch takes 64-slot chunks from the queues directly.
+//    dry mid-epoch takes slots from the queues directly.
 //  - The slot range is split into one partition per XCD; windows and chunks come from the XCD's own
 //    partition first and from the others only when it is empty. Each XCD's L2 then holds its own band
 //    of the DEM (or its own runs).
-//  - Every run writes the caller's rasters directly (a single run v^2 bits, turned into speeds by a finalize pass, a
-//    batch's runs the speeds).
-//    Per-XCD private copies bought nothing once the table had cut the atomics: the atomics are
-//    performed at the memory side either way, and zeroing and merging the copies cost 9 % at 8192^2.
+//  - Every run writes the caller's rasters directly (a single run v^2 bits, turned into speeds by a finalize
+//    pass, a batch's runs the speeds). Per-XCD private copies bought nothing once the table had cut the
+//    atomics: the atomics are performed at the memory side either way, and zeroing and merging the copies
+//    cost 9 % at 8192^2.
 //  - Accumulation is integer only (u32 add; u32 max on the bits of v^2 >= 0, whose order is the value
 //    order), so every raster is independent of scheduling and of the kernel variant: bit-reproducible.
 //  - Philox4x32-10 gives four words per block; one block serves two consecutive steps.

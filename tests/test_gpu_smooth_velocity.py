@@ -1,4 +1,4 @@
-"""The velocity raster's table: every forward variant, releases close together (cells shared, several flushes) and scattered
+"""The velocity raster, through its table and (few particles) straight: every forward variant, releases close together (cells shared, several flushes) and scattered
 (buckets overflow to the raster), masses whose fixed point needs 64 bits, one and several slots per lane."""
 import numpy as np
 import pytest
@@ -17,7 +17,8 @@ def avl():
     return m
 
 
-@pytest.mark.parametrize("density,P,mass_scale", [(0.02, 40, 1.0), (0.3, 1, 1.0), (0.05, 3, 5000.0), (0.001, 1, 1.0)])
+@pytest.mark.parametrize("density,P,mass_scale", [(0.02, 40, 1.0), (0.3, 1, 1.0), (0.05, 3, 5000.0), (0.001, 1, 1.0),
+                                                  (0.002, 17, 3000.0), (0.05, 17, 5000.0)])
 def test_velocity_raster_every_variant(avl, density, P, mass_scale):
     dem = synth.incline_fillet_dem(160, 10.0, seed=5)[:, :131].copy()
     rng = np.random.default_rng(8)
