@@ -253,7 +253,7 @@ AVL_API size_t avl_batched_workspace_bytes(int32_t H, int32_t W, int32_t n_tiles
  * run releases no particle and leaves zero rasters). particles_per_cell and step_limit are shared.
  * Need H, W < 2^23, n_runs*H*W, n_tiles*H*W, n_masks*H*W and n_tiles*(H+2)*(W+2) all < 2^32 - 1 and
  * (H+2)*(W+2) < 2^30 (the kernel reads padded copies of the tiles through 32-bit offsets). When `stream` is not the null stream, the
- * whole sequence (zero fills, compactions, run setup, trajectory kernel, finalize) is captured once into
+ * whole sequence (preparation, release lists, run setup, start records, trajectory kernel) is captured once into
  * a HIP graph per argument set and replayed on later calls. */
 AVL_API int avl_trajectories_batched(const float* dems, int32_t n_tiles, const uint8_t* masks, int32_t n_masks,
                                      int32_t H, int32_t W, float cell_size, const avl_params* params,
@@ -362,7 +362,7 @@ AVL_API int avl_set_smooth_tuning(int32_t forward_variant, int32_t backward_vari
  * for a NULL pointer. */
 AVL_API int avl_smooth_tuning_variants(int32_t* n_forward, int32_t* n_backward);
 /* Shape of a kernel variant: info (8 host int32) = threads per block, iterations per epoch between table
- * flushes, LDS table slots per block, probes per key, window top-up in blocks of slots, retention threshold
+ * flushes, LDS table slots per block, candidate slots per key, window top-up in blocks of slots, retention threshold
  * (0 = none), waves per SIMD the register budget is sized for, particle slots per lane that size the grid of a
  * small problem. AVL_EINVAL for a NULL info or an index out of range. */
 AVL_API int avl_tuning_variant_info(int32_t variant, int32_t* info);
