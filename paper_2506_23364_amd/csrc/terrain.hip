@@ -37,8 +37,10 @@ __device__ __forceinline__ float4 normal_of(float dx, float dy, float sx, float 
         const float q = a * r;
         return __builtin_fmaf(__builtin_fmaf(-b, q, a), r, q);
     };
-    auto in_range = [](float d, float g) {  // |g| in [2^-60, 2^60], or the difference is 0
-        return d == 0.0f || (__float_as_uint(g) & 0x7FFFFFFFu) - 0x21800000u <= 0x5D800000u - 0x21800000u;
+    // |g| in [2^-60, 2^60], or the difference is +0; one of -0 (+0.0 and -0.0 side by side) keeps its sign only in a division,
+    // for the residual step adds a +0
+    auto in_range = [](float d, float g) {
+        return __float_as_uint(d) == 0u || (__float_as_uint(g) & 0x7FFFFFFFu) - 0x21800000u <= 0x5D800000u - 0x21800000u;
     };
     float gx = quotient(dx, sx, rx), gy = quotient(dy, sy, ry);
     float gg = gx * gx + gy * gy;

@@ -66,3 +66,18 @@ def test_mipmap_of_every_remainder(avl, h, w):
         for (gc, gv), (rc, rv) in zip(got, ref):
             assert np.array_equal(gc.cpu().numpy(), rc)
             assert np.array_equal(gv.cpu().numpy(), rv)
+
+
+@pytest.mark.parametrize("scale", [0.0, 3.0])
+def test_normals_keep_the_sign_of_a_zero_difference(avl, scale):
+    # a raster multiplied by a mask has zeros of both signs: -0.0 beside +0.0 is a difference of -0.0
+    rng = np.random.default_rng(23)
+    dem = (rng.standard_normal((41, 133)) * scale).astype(np.float32)
+    sea = rng.random(dem.shape) < 0.7
+    dem[sea] = np.where(rng.random(int(sea.sum())) < 0.5, np.float32(-0.0), np.float32(0.0))
+    want = oracle.normals(dem, 10.0)
+    assert np.signbit(want[want[..., 0] == 0.0][:, 0]).any() and not np.signbit(want[want[..., 0] == 0.0][:, 0]).all()
+    got = avl.normals(dev(dem), 10.0).cpu().numpy()
+    assert np.array_equal(got[..., :3].view(np.uint32), want[..., :3].view(np.uint32))
+    both, _ = avl.normals_release_mask(dev(dem), 10.0, 30.0, 45.0, -np.inf, np.inf)
+    assert np.array_equal(both.cpu().numpy().view(np.uint32), got.view(np.uint32))
