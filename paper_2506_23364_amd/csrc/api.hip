@@ -1376,6 +1376,7 @@ struct CalibWs {
     float* gD;         // H*W
     double* part;      // loss partial sums
     int32_t* status;   // smooth pass status
+    unsigned long long* slots;  // the iteration's particles
     avl::RunSpec* spec;  // the run, on the device
     avl_params* p;       // the current parameters, on the device
     double* state;       // Adam's state (avl::kCalibState)
@@ -1397,6 +1398,7 @@ size_t calib_layout(int32_t H, int32_t W, int32_t max_cells, uint32_t P, uint32_
     char* g = take((size_t)n * 4);
     char* pt = take(avl::mse_partials() * sizeof(double));
     char* sc = take(sizeof(int32_t));
+    char* sl = take(sizeof(unsigned long long));
     char* spc = take(sizeof(avl::RunSpec));
     char* pp = take(sizeof(avl_params));
     char* stt = take(avl::kCalibState * sizeof(double));
@@ -1409,6 +1411,7 @@ size_t calib_layout(int32_t H, int32_t W, int32_t max_cells, uint32_t P, uint32_
         c->gD = reinterpret_cast<float*>(g);
         c->part = reinterpret_cast<double*>(pt);
         c->status = reinterpret_cast<int32_t*>(sc);
+        c->slots = reinterpret_cast<unsigned long long*>(sl);
         c->spec = reinterpret_cast<avl::RunSpec*>(spc);
         c->p = reinterpret_cast<avl_params*>(pp);
         c->state = reinterpret_cast<double*>(stt);
@@ -1487,6 +1490,7 @@ int avl_calibrate(const float* dem, const uint8_t* mask, const float* mass, int3
     step.next = setup_of(sw, *start, cell_size, particles_per_cell, seed, run_id, max_release_cells, c.status, c.p, c.spec);
     step.n_cells = sw.w.n_cells;
     step.stats = sw.w.stats;
+    step.slots = c.slots;
     unsigned long long* const dep_q = reinterpret_cast<unsigned long long*>(c.dep_q);
     for (int32_t t = 0; t < n_iters; ++t) {
         // after the first pass the release cells, padded DEM, start records and masses are in the workspace, and each
@@ -1495,7 +1499,8 @@ int avl_calibrate(const float* dem, const uint8_t* mask, const float* mass, int3
                                  run_id, max_release_cells, 0u, c.dep_q, nullptr, nullptr, nullptr, nullptr, c.status,
                                  c.smooth, c.smooth_bytes, stream, t > 0, c.p, c.spec)) != AVL_OK)
             return drained(rc);
-        if ((e = avl::launch_calib_loss(dep_q, target, n, cgrad, c.gD, c.part, sw.w.queues, s)) != hipSuccess)
+        if ((e = avl::launch_calib_loss(dep_q, target, n, cgrad, c.gD, c.part, sw.w.queues, sw.w.runs, c.slots, s)) !=
+            hipSuccess)
             return drained(hip_fail(e, "avl_calibrate: loss"));
         const int32_t slot = t % kCalibRows;
         step.row = c.hist + 5 * slot;

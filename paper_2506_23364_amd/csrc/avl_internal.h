@@ -316,10 +316,10 @@ constexpr int kCalibState = 8;
 hipError_t launch_calib_init(RunSpec spec, ::avl_params start, RunSpec* spec_dev, ::avl_params* p_dev, double* state,
                              int32_t* err, hipStream_t s);
 // The loss between the two passes of an iteration: gD = c (D - T) with D from the deposit's fixed point, and the partial
-// sums of (D - T)^2 (binary64, fixed order). It leaves dep_q cleared for the next iteration's forward and the queues for
-// this one's adjoint.
+// sums of (D - T)^2 (binary64, fixed order). It leaves dep_q cleared for the next iteration's forward, the queues for
+// this one's adjoint, and in *slots the run's particles for the sums at the iteration's end.
 hipError_t launch_calib_loss(unsigned long long* dep_q, const float* target, int64_t n, float c, float* gD, double* part,
-                             unsigned long long* queues, hipStream_t s);
+                             unsigned long long* queues, const RunConst* runs, unsigned long long* slots, hipStream_t s);
 // The end of an iteration: L from the partial sums, dL/dparams of the adjoint, one Adam step on them; writes the history row
 // (loss, mu, xi, dL/dmu, dL/dxi, before the step), updates the state and the parameters; the first iteration whose
 // pass reported a nonzero status is kept in err = (status, iteration). Then it clears the queues and the statistics and
@@ -336,6 +336,7 @@ struct CalibStep {
     SetupOne next;  // its status is the pass's own until then
     const int32_t* n_cells;
     unsigned long long* stats;
+    const unsigned long long* slots;  // this iteration's particles (launch_calib_loss)
 };
 hipError_t launch_calib_step(const SmoothArgs& a, double* part, const CalibStep& c, hipStream_t s);
 hipError_t launch_finalize_vmax(uint32_t* vmax_bits, int64_t n, hipStream_t s);

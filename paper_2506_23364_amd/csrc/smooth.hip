@@ -674,6 +674,7 @@ struct ReduceArgs {
     const float* pp;
     unsigned long long cap;
     const RunConst* runs;
+    const unsigned long long* n_slots;  // particles; nothing writes it while the sums run
     double* part;  // 3 a.nb
     double* out;   // 3, nullable
     unsigned long long* queues;
@@ -697,7 +698,7 @@ __device__ __forceinline__ void tree_sum3(double (&sh)[3][kReduceThreads], const
 // them to a.out (unless null).
 __device__ __forceinline__ bool reduce_params(const ReduceArgs& a, double (&sh)[3][kReduceThreads]) {
     __shared__ uint32_t rank;
-    const unsigned long long n = a.runs[0].n_slots;
+    const unsigned long long n = *a.n_slots;
     const uint32_t used = max(1u, (uint32_t)((n + kReduceChunk - 1) / kReduceChunk));  // blocks that hold particles
     if (blockIdx.x >= used) return false;
     const unsigned long long base = (unsigned long long)blockIdx.x * kReduceChunk + threadIdx.x * 16ull;
@@ -832,9 +833,14 @@ __device__ __forceinline__ void clear_queues(unsigned long long* queues) {
 __global__ __launch_bounds__(kMseThreads) void k_calib_loss(unsigned long long* __restrict__ dep_q,
                                                             const float* __restrict__ tgt, int64_t n, float c,
                                                             float* __restrict__ gD, double* __restrict__ part,
-                                                            unsigned long long* __restrict__ queues) {
+                                                            unsigned long long* __restrict__ queues,
+                                                            const RunConst* __restrict__ runs,
+                                                            unsigned long long* __restrict__ slots) {
     __shared__ double lds[kMseThreads / kWave];
-    if (blockIdx.x == 0) clear_queues(queues);
+    if (blockIdx.x == 0) {
+        clear_queues(queues);
+        if (threadIdx.x == 0) *slots = runs[0].n_slots;
+    }
     double acc = 0.0;
     for (int64_t i = (int64_t)blockIdx.x * kMseThreads + threadIdx.x; i < n; i += (int64_t)kMseBlocks * kMseThreads) {
         const float d = q_value(dep_q[i]) - tgt[i];
@@ -847,8 +853,9 @@ __global__ __launch_bounds__(kMseThreads) void k_calib_loss(unsigned long long* 
 }
 
 hipError_t launch_calib_loss(unsigned long long* dep_q, const float* target, int64_t n, float c, float* gD, double* part,
-                             unsigned long long* queues, hipStream_t s) {
-    hipLaunchKernelGGL(k_calib_loss, dim3(kMseBlocks), dim3(kMseThreads), 0, s, dep_q, target, n, c, gD, part, queues);
+                             unsigned long long* queues, const RunConst* runs, unsigned long long* slots, hipStream_t s) {
+    hipLaunchKernelGGL(k_calib_loss, dim3(kMseBlocks), dim3(kMseThreads), 0, s, dep_q, target, n, c, gD, part, queues, runs,
+                       slots);
     return hipGetLastError();
 }
 
@@ -896,6 +903,8 @@ __device__ void adam_step(const CalibStep& a, double loss, const double* g3) {
     a.p->xi = (float)st[1];
 }
 
+// The block that finishes last writes the next iteration's run table and clears the ticket, while blocks that hold no
+// particles may not have started yet: they read the number of particles from c.slots, which the loss kernel wrote, and leave.
 __global__ __launch_bounds__(kReduceThreads) void k_calib_step(ReduceArgs a, CalibStep c, int32_t H, int32_t W) {
     static_assert(kReduceThreads == kMseThreads, "the loss sums in this order");
     __shared__ double sum[3][kReduceThreads];
@@ -978,14 +987,14 @@ hipError_t launch_smooth_backward_kernel(const SmoothArgs& a, int variant, hipSt
 
 hipError_t launch_smooth_reductions(const SmoothArgs& a, const int32_t* n_cells, float* dmass, int64_t max_cells,
                                     double* part, double* dparams, hipStream_t s) {
-    ReduceArgs r{a.pp, a.cap, a.runs, part, dparams, a.queues, (uint32_t)smooth_reduce_blocks(a.cap), a.cells, n_cells, dmass};
+    ReduceArgs r{a.pp, a.cap, a.runs, &a.runs->n_slots, part, dparams, a.queues, (uint32_t)smooth_reduce_blocks(a.cap), a.cells, n_cells, dmass};
     const int64_t mass = std::min<int64_t>((max_cells + 63) / 64, 4096);  // 16 cells a wave, then the next ones
     hipLaunchKernelGGL(k_smooth_reduce, dim3(r.nb + (uint32_t)mass), dim3(kReduceThreads), 0, s, r);
     return hipGetLastError();
 }
 
 hipError_t launch_calib_step(const SmoothArgs& a, double* part, const CalibStep& c, hipStream_t s) {
-    ReduceArgs r{a.pp, a.cap, a.runs, part, nullptr, a.queues, (uint32_t)smooth_reduce_blocks(a.cap), a.cells, nullptr, nullptr};
+    ReduceArgs r{a.pp, a.cap, a.runs, c.slots, part, nullptr, a.queues, (uint32_t)smooth_reduce_blocks(a.cap), a.cells, nullptr, nullptr};
     hipLaunchKernelGGL(k_calib_step, dim3(r.nb), dim3(kReduceThreads), 0, s, r, c, a.H, a.W);
     return hipGetLastError();
 }
