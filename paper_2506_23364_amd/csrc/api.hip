@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "avl_internal.h"
+#include "tuning.h"
 
 // Scratch of avl_trajectories_noalloc: the single-run workspace in a file-scope device array, one copy per
 // GPU, which the code object's loader places in device memory and which lives until the process ends.
@@ -229,19 +230,10 @@ int32_t g_smooth_override[2] = {-1, -1};  // smooth forward, adjoint
 bool g_graphs = true;
 std::map<std::vector<int64_t>, int> g_best;  // (device, batched, size buckets) -> variant
 
-int ilog2(uint64_t v) {
-    int r = 0;
-    while (v > 1) {
-        v >>= 1;
-        ++r;
-    }
-    return r;
-}
-
-std::vector<int64_t> tune_key(bool batched, int64_t n, int64_t n_runs, uint32_t P, uint32_t S) {
+int current_device() {
     int dev = 0;
     (void)hipGetDevice(&dev);
-    return {dev, batched ? 1 : 0, ilog2((uint64_t)n), ilog2((uint64_t)n_runs), ilog2(P), ilog2((uint64_t)S + 1)};
+    return dev;
 }
 
 bool capturing(hipStream_t s) {
@@ -373,12 +365,6 @@ hipError_t choose_smooth(const std::vector<int64_t>& key, int nv, hipStream_t s,
     g_best[key] = best;
     *variant = best;
     return hipSuccess;
-}
-
-std::vector<int64_t> smooth_key(int kind, int64_t n, int64_t cap, uint32_t P, uint32_t S) {
-    int dev = 0;
-    (void)hipGetDevice(&dev);
-    return {dev, kind, ilog2((uint64_t)n), ilog2((uint64_t)cap + 1), ilog2(P), ilog2((uint64_t)S + 1)};
 }
 
 // ------------------------------------------------------------------ graph cache of batched calls
@@ -778,8 +764,8 @@ int single_pass(const char* where, const float* dem, const uint8_t* mask, int32_
     }
     int variant = 0;
     bool tuned = false;
-    if ((e = choose_variant(a, false, tune_key(false, nf, 1, particles_per_cell, step_limit), s, zero, &variant, &tuned,
-                            !noalloc)) != hipSuccess)
+    if ((e = choose_variant(a, false, avl::tune_key(current_device(), false, nf, 1, particles_per_cell, step_limit), s,
+                            zero, &variant, &tuned, !noalloc)) != hipSuccess)
         return hip_fail(e, (std::string(where) + ": autotune").c_str());
     g_last_variant = variant;
     if (tuned && (e = zero()) != hipSuccess) return hip_fail(e, (std::string(where) + ": zero").c_str());
@@ -1119,7 +1105,8 @@ int smooth_forward(const float* dem, const uint8_t* mask, const float* mass, int
     }
     int variant = 0;
     bool tuned = false;
-    if ((e = choose_smooth(smooth_key(2, n, max_release_cells, particles_per_cell, step_limit),
+    if ((e = choose_smooth(avl::smooth_key(current_device(), 2, n, max_release_cells, particles_per_cell, step_limit,
+                                           vel),
                            avl::smooth_forward_variants(), s, zero,
                            [&](int v) { return avl::launch_smooth_forward(a, v, s); }, &variant, &tuned)) != hipSuccess)
         return hip_fail(e, "avl_trajectories_smooth: autotune");
@@ -1172,7 +1159,8 @@ int smooth_backward(const float* dem, const uint8_t* mask, const float* mass, in
     auto zero = [&]() -> hipError_t { return avl::launch_prepare(clear, s); };
     int variant = 0;
     bool tuned = false;
-    if ((e = choose_smooth(smooth_key(3, n, max_release_cells, particles_per_cell, step_limit),
+    if ((e = choose_smooth(avl::smooth_key(current_device(), 3, n, max_release_cells, particles_per_cell, step_limit,
+                                           false),
                            avl::smooth_backward_variants(), s, zero,
                            [&](int v) { return avl::launch_smooth_backward_kernel(a, v, s); }, &variant, &tuned)) !=
         hipSuccess)
@@ -1300,7 +1288,7 @@ int avl_trajectories_batched(const float* dems, int32_t n_tiles, const uint8_t* 
     // the variant is chosen eagerly, before any capture (tuning runs need the run table in place)
     hipError_t e;
     int variant = 0;
-    const std::vector<int64_t> tkey = tune_key(true, n, n_runs, particles_per_cell, step_limit);
+    const std::vector<int64_t> tkey = avl::tune_key(current_device(), true, n, n_runs, particles_per_cell, step_limit);
     bool known = false;
     {
         std::lock_guard<std::mutex> lk(g_mu);
