@@ -764,8 +764,9 @@ int single_pass(const char* where, const float* dem, const uint8_t* mask, int32_
     }
     int variant = 0;
     bool tuned = false;
-    if ((e = choose_variant(a, false, avl::tune_key(current_device(), false, nf, 1, particles_per_cell, step_limit), s,
-                            zero, &variant, &tuned, !noalloc)) != hipSuccess)
+    if ((e = choose_variant(a, false, avl::tune_key(current_device(), false, nf, 1, particles_per_cell, step_limit,
+                                              a.runout_angle != 0u),
+                            s, zero, &variant, &tuned, !noalloc)) != hipSuccess)
         return hip_fail(e, (std::string(where) + ": autotune").c_str());
     g_last_variant = variant;
     if (tuned && (e = zero()) != hipSuccess) return hip_fail(e, (std::string(where) + ": zero").c_str());
@@ -1288,7 +1289,8 @@ int avl_trajectories_batched(const float* dems, int32_t n_tiles, const uint8_t* 
     // the variant is chosen eagerly, before any capture (tuning runs need the run table in place)
     hipError_t e;
     int variant = 0;
-    const std::vector<int64_t> tkey = avl::tune_key(current_device(), true, n, n_runs, particles_per_cell, step_limit);
+    const std::vector<int64_t> tkey =
+        avl::tune_key(current_device(), true, n, n_runs, particles_per_cell, step_limit, false);
     bool known = false;
     {
         std::lock_guard<std::mutex> lk(g_mu);

@@ -17,8 +17,12 @@ inline int ilog2(uint64_t v) {
     return r;
 }
 
-inline std::vector<int64_t> tune_key(int dev, bool batched, int64_t n, int64_t n_runs, uint32_t P, uint32_t S) {
-    return {dev, batched ? 1 : 0, ilog2((uint64_t)n), ilog2((uint64_t)n_runs), ilog2(P), ilog2((uint64_t)S + 1)};
+// runout: a single run with the runout-angle stop runs an instantiation of its own (a batch always has the stop compiled in).
+// With one choice for both, a 1001 x 1203 pass of 32 particles a texel without the stop took 394 us after one with it, 356 with
+// a shape of its own.
+inline std::vector<int64_t> tune_key(int dev, bool batched, int64_t n, int64_t n_runs, uint32_t P, uint32_t S, bool runout) {
+    return {dev, batched ? 1 : 0, ilog2((uint64_t)n), ilog2((uint64_t)n_runs), ilog2(P), ilog2((uint64_t)S + 1),
+            runout && !batched ? 1 : 0};
 }
 
 // velocity: the forward with the velocity raster is a kernel of its own (other tables, a barrier every few steps), so a

@@ -1,4 +1,4 @@
-// Prints the tuner's keys of the problems given on the command line, one line each: "t batched n runs P S" or
+// Prints the tuner's keys of the problems given on the command line, one line each: "t batched n runs P S runout" or
 // "s kind n cap P S velocity".
 #include <cstdio>
 #include <cstdlib>
@@ -10,12 +10,12 @@ int main(int argc, char** argv) {
     for (int i = 1; i < argc;) {
         const bool smooth = std::strcmp(argv[i], "s") == 0;
         long long v[6] = {};
-        const int n = smooth ? 6 : 5;
-        if (i + n >= argc) return 1;
-        for (int k = 0; k < n; ++k) v[k] = std::atoll(argv[i + 1 + k]);
-        i += n + 1;
+        const int n = 6;
+        if (i + 6 >= argc) return 1;
+        for (int k = 0; k < 6; ++k) v[k] = std::atoll(argv[i + 1 + k]);
+        i += 7;
         const auto key = smooth ? avl::smooth_key(0, (int)v[0], v[1], v[2], (uint32_t)v[3], (uint32_t)v[4], v[5] != 0)
-                                : avl::tune_key(0, v[0] != 0, v[1], v[2], (uint32_t)v[3], (uint32_t)v[4]);
+                                : avl::tune_key(0, v[0] != 0, v[1], v[2], (uint32_t)v[3], (uint32_t)v[4], v[5] != 0);
         for (auto k : key) std::printf("%lld ", (long long)k);
         std::printf("\n");
     }

@@ -32,5 +32,12 @@ def test_velocity_forward_has_a_choice_of_its_own(keys, n, cap, P, S):
 def test_sizes_share_a_choice_by_powers_of_two(keys):
     a, b, c = keys(("s", 2, 40000, 600, 10, 1000, 1), ("s", 2, 65535, 1000, 15, 1022, 1), ("s", 2, 65536, 600, 10, 1000, 1))
     assert a == b != c
-    a, b, c = keys(("t", 0, 40000, 1, 10, 1000), ("t", 0, 65535, 1, 15, 1022), ("t", 1, 40000, 1, 10, 1000))
+    a, b, c = keys(("t", 0, 40000, 1, 10, 1000, 0), ("t", 0, 65535, 1, 15, 1022, 0),
+                   ("t", 1, 40000, 1, 10, 1000, 0))
     assert a == b != c
+
+
+def test_runout_stop_has_a_choice_of_its_own(keys):
+    off, on, batch_off, batch_on = keys(*[("t", b, 1 << 22, 4, 32, 2000, r) for b in (0, 1) for r in (0, 1)])
+    assert off != on
+    assert batch_off == batch_on != off  # a batch always has the stop compiled in
