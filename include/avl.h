@@ -355,8 +355,10 @@ AVL_API int avl_set_tuning(int32_t variant, int32_t graphs);
 AVL_API int32_t avl_tuning_variants(void);
 /* The same for the smooth forward (avl_trajectories_smooth) and its adjoint (avl_trajectories_backward):
  * -1 lets the library's tuner pick a grid shape per problem size, else a fixed variant index in
- * [0, n) with n from avl_smooth_tuning_variants (grid shapes only: every variant gives identical
- * results). Returns AVL_EINVAL for an out-of-range index. */
+ * [0, n) with n from avl_smooth_tuning_variants (forward: the grid shapes, then the same shapes with the velocity
+ * splats of middling releases of few particles a cell straight to the raster at first and through a table in
+ * LDS later, which other passes do not tell apart; adjoint: particles a block sorts by path length; every
+ * variant gives identical results). Returns AVL_EINVAL for an out-of-range index. */
 AVL_API int avl_set_smooth_tuning(int32_t forward_variant, int32_t backward_variant);
 /* Number of smooth forward and adjoint variants into *n_forward, *n_backward (host pointers); AVL_EINVAL
  * for a NULL pointer. */

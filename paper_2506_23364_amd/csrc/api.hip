@@ -319,7 +319,7 @@ hipError_t choose_smooth(const std::vector<int64_t>& key, int nv, hipStream_t s,
         std::lock_guard<std::mutex> lk(g_mu);
         const int32_t forced = g_smooth_override[key[1] == 2 ? 0 : 1];
         if (forced >= 0) {
-            *variant = forced < nv ? forced : 0;
+            *variant = forced % nv;  // the second half repeats the shapes where it would not differ
             return hipSuccess;
         }
         auto it = g_best.find(key);
@@ -1108,7 +1108,7 @@ int smooth_forward(const float* dem, const uint8_t* mask, const float* mass, int
     bool tuned = false;
     if ((e = choose_smooth(avl::smooth_key(current_device(), 2, n, max_release_cells, particles_per_cell, step_limit,
                                            vel),
-                           avl::smooth_forward_variants(), s, zero,
+                           avl::smooth_forward_variants(vel, particles_per_cell), s, zero,
                            [&](int v) { return avl::launch_smooth_forward(a, v, s); }, &variant, &tuned)) != hipSuccess)
         return hip_fail(e, "avl_trajectories_smooth: autotune");
     if (tuned && (e = zero()) != hipSuccess) return hip_fail(e, "avl_trajectories_smooth: zero");

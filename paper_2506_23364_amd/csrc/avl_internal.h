@@ -282,6 +282,7 @@ struct SmoothArgs {
     const float* dem_pad;                   // the DEM with a replicated border, (H + 2) x (W + 2)
     uint32_t pad_bytes;                     // its bytes, < 2^32
     uint32_t spl;                           // forward: particle slots per lane of a small problem (set by the launcher)
+    uint32_t direct;                        // forward: the velocity starts straight where it may (set by the launcher)
     uint32_t window;                        // adjoint: particles a block sorts by path length (set by the launcher)
     const StartRec* starts;                 // per release cell: the start state of its particles
     const float* mpc;                       // per release cell: the mass of each of its particles
@@ -295,7 +296,7 @@ size_t smooth_scratch_bytes();
 size_t smooth_reduce_blocks(unsigned long long cap);
 // Kernel variants of the smooth forward and of the adjoint (grid shapes only: every variant gives the same
 // results); the library's tuner picks one per problem size.
-int smooth_forward_variants();
+int smooth_forward_variants(bool velocity = true, uint32_t P = 1);  // those that differ for such a pass
 int smooth_backward_variants();
 hipError_t launch_smooth_forward(const SmoothArgs& a, int variant, hipStream_t s);
 hipError_t launch_smooth_backward_kernel(const SmoothArgs& a, int variant, hipStream_t s);

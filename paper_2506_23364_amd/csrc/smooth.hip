@@ -20,6 +20,7 @@
 
 #include "particle.h"
 #include "setup.h"
+#include "tuning.h"
 
 namespace avl {
 
@@ -235,18 +236,9 @@ __device__ __forceinline__ uint64_t cell_of_slot(uint64_t slot, const SmoothArgs
 }  // namespace
 
 // kBlk threads per block share the tables; a.spl particle slots per lane size the grid of a small problem. With kVel every
-// accepted step also splats the velocity raster, through a table that the block flushes every kVelPairs pairs of steps.
-// Few particles stay below the rate of the memory side's adds, which nothing waits for, while the table's round trips and
-// barriers lengthen each step; and the fewer particles share a release cell, the fewer splats the table can merge. So up to
-// kDirectSlots particles, or 2 kDirectSlots at eight a cell and with the square of their number up to 128 kDirectSlots at
-// one, the velocity goes straight to the raster. Short paths, direct against table: 2470 particles of 10 a cell 63 against
-// 76 us, 6000 of 10 69/80, 12,000 of 40 115/75; 80,000 of 1 203/304, 80,000 of 4 204/246, 320,000 of 4 555/361. Long paths:
-// 1600 of 8 183/199, 6000 of 10 263/207, 12,000 of 40 489/200, 12,000 of 4 254/267, 10,000 of 1 232/386.
-constexpr int kVelPairs = 16;
-constexpr unsigned long long kDirectSlots = 3072;
-__device__ __forceinline__ bool velocity_direct(unsigned long long slots, uint32_t P) {
-    return slots <= kDirectSlots || (P <= 8u && slots * P * P <= 128u * kDirectSlots);
-}
+// accepted step also splats the velocity raster, through a table that the block flushes every kVelPairs pairs of steps, or
+// straight, or straight for the first kStraightPairs pairs where the tuner chose that (tuning.h).
+constexpr int kVelPairs = 16, kStraightPairs = 32, kAllPairs = 0x7FFFFFFF;
 template <int kBlk, bool kVel>
 __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
     if ((uint64_t)blockIdx.x >= active_blocks(a.run_off[1], kBlk, a.spl)) return;  // small problems: fewer blocks
@@ -278,7 +270,13 @@ __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
         }
     }
     __syncthreads();
-    const bool direct = kVel && velocity_direct(rc.n_slots, rc.P);
+    bool direct = false;
+    int pairs = kAllPairs;  // until the table's next flush
+    if constexpr (kVel) {
+        const bool always = velocity_straight(rc.n_slots, rc.P);
+        direct = always || (a.direct != 0u && velocity_straight_first(rc.n_slots, rc.P));
+        if (!always) pairs = direct ? kStraightPairs : kVelPairs;
+    }
 
     bool alive = false;
     State s{};
@@ -355,7 +353,7 @@ __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
     // particle starts from its release cell's start record (one load, the mass per particle beside it).
     for (;;) {
         bool finished = false;
-        for (int pair = 0; !kVel || direct || pair < kVelPairs; ++pair) {
+        for (int pair = 0; !kVel || pair < pairs; ++pair) {
             const uint64_t idle = __ballot(!alive);
             const bool drained = disp.drained();
             if (__popcll(idle) == kWave && drained) {
@@ -390,7 +388,9 @@ __global__ __launch_bounds__(kBlk) void k_smooth_forward(SmoothArgs a) {
             advance(o.x, o.y, true);
             advance(o.z, o.w, false);
         }
-        if (!kVel || direct) break;
+        if (!kVel || pairs == kAllPairs) break;
+        direct = false;
+        pairs = kVelPairs;
         __syncthreads();
         for (int k = threadIdx.x; k < kVelSlots; k += kBlk) {
             if (vel.tag[k] != kDepEmpty) {
@@ -942,7 +942,8 @@ struct SmoothVariant {
 };
 // Forward candidates: (threads per block, slots per lane). Small blocks with a slot per lane serve problems that leave SIMDs
 // idle otherwise (96,000 particles: 52 us with 1024 threads or two slots, 47 so). The first is kept unless another is
-// faster, and holds for the larger problems of its size class too, since it leaves no lane a second round.
+// faster, and holds for the larger problems of its size class too, since it leaves no lane a second round. With the velocity
+// raster and few particles a cell each shape is a candidate twice, the second time starting straight where it may.
 constexpr SmoothVariant kFwdVariants[] = {{256, 1}, {1024, 2}, {512, 2}, {1024, 1}, {256, 8}, {512, 1}};
 // adjoint candidates: particles of a window
 constexpr uint32_t kBwdWindows[] = {1024, 512, 256, 2048};
@@ -962,12 +963,17 @@ void launch_fwd(const SmoothArgs& a, hipStream_t s) {
 
 }  // namespace
 
-int smooth_forward_variants() { return (int)(sizeof(kFwdVariants) / sizeof(kFwdVariants[0])); }
+constexpr int kFwdShapes = (int)(sizeof(kFwdVariants) / sizeof(kFwdVariants[0]));
+int smooth_forward_variants(bool velocity, uint32_t P) {
+    return velocity && P <= kStraightReplicas ? 2 * kFwdShapes : kFwdShapes;
+}
 int smooth_backward_variants() { return (int)(sizeof(kBwdWindows) / sizeof(kBwdWindows[0])); }
 
 hipError_t launch_smooth_forward(const SmoothArgs& a, int variant, hipStream_t s) {
-    if (variant < 0 || variant >= smooth_forward_variants()) variant = 0;
+    if (variant < 0 || variant >= 2 * kFwdShapes) variant = 0;
     SmoothArgs b = a;
+    b.direct = variant >= kFwdShapes ? 1u : 0u;
+    variant %= kFwdShapes;
     b.spl = kFwdVariants[variant].spl;
     switch (kFwdVariants[variant].block) {
         case 1024: b.vel_q ? launch_fwd<1024, true>(b, s) : launch_fwd<1024, false>(b, s); break;
