@@ -178,7 +178,7 @@ struct Fill {
     uint32_t v;
 };
 constexpr int kFills = 6;
-// One launch: fills, padded copies of the DEM tiles (dem null: none; (H + 2) x (W + 2) each, edge texels replicated
+// One launch (more only past 2^23 blocks): fills, padded copies of the DEM tiles (dem null: none; (H + 2) x (W + 2) each, edge texels replicated
 // into a one-texel border) and the counts of nonzero bytes per kScanChunk texels of each mask (mask null: none).
 struct PrepArgs {
     Fill fill[kFills];
@@ -191,7 +191,7 @@ struct PrepArgs {
     uint32_t n_masks;
     uint32_t* blk;  // n_masks x scan_blocks(n)
     // set by the launcher
-    uint32_t nb, count_blocks, pad_nb, pad_blocks, fill_blocks[kFills];
+    uint32_t first, nb, count_blocks, pad_nb, pad_blocks, fill_blocks[kFills];
     DivU32 wpdiv;
 };
 hipError_t launch_prepare(PrepArgs a, hipStream_t s);

@@ -111,7 +111,7 @@ __device__ __forceinline__ void fill_role(const Fill& f, uint32_t block) {
 }
 
 __global__ __launch_bounds__(kPrepThreads) void k_prepare(PrepArgs a) {
-    uint32_t b = blockIdx.x;
+    uint32_t b = a.first + blockIdx.x;
     if (b < a.count_blocks) {
         const uint32_t m = b / a.nb, chunk = b - m * a.nb;
         const int64_t base = (int64_t)chunk * kScanChunk + (int64_t)threadIdx.x * kScanPerThread;
@@ -158,10 +158,16 @@ hipError_t launch_prepare(PrepArgs a, hipStream_t s) {
         a.fill_blocks[k] = (uint32_t)nb;
         total += nb;
     }
-    if (total == 0) return hipSuccess;
-    if (total >= (uint64_t(1) << 31)) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_prepare, dim3((unsigned)total), dim3(kPrepThreads), 0, s, a);
-    return hipGetLastError();
+    // a launch holds less than 2^32 threads, and a batch of very many small tiles or masks has a block for each; its entry
+    // limits keep the blocks of all roles below 2^32
+    constexpr uint64_t kMaxBlocks = uint64_t(1) << 23;
+    hipError_t e = hipSuccess;
+    for (uint64_t at = 0; at < total && e == hipSuccess; at += kMaxBlocks) {
+        a.first = (uint32_t)at;
+        hipLaunchKernelGGL(k_prepare, dim3((unsigned)std::min(total - at, kMaxBlocks)), dim3(kPrepThreads), 0, s, a);
+        e = hipGetLastError();
+    }
+    return e;
 }
 
 // ------------------------------------------------------------------------------------------ scan of the counts

@@ -55,3 +55,22 @@ def test_batch_of_odd_tiles(avl):
         ref = oracle.trajectories(dems[t], masks[s], 5.0, oracle.make_params(**p), 4, 80, seed, run_id)
         assert np.array_equal(r.counts[k].cpu().numpy(), ref.counts), k
         np.testing.assert_allclose(r.vmax[k].cpu().numpy(), ref.vmax, rtol=1e-5, atol=0)
+
+
+def test_batch_of_more_small_tiles_than_one_launch_holds(avl):
+    # a block per tile and per mask: 2^24 blocks of 256 threads would be 2^32 threads
+    n = (1 << 24) + 5
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    dems = torch.rand(n, 2, 2, device="cuda", generator=g) * 30.0
+    masks = (torch.rand(n, 2, 2, device="cuda", generator=g) < 0.5).to(torch.uint8)
+    p = dict(synth.DEFAULT_PARAMS, mu=0.1)
+    at = [0, 1, (1 << 23) - 1, 1 << 23, (1 << 24) - 1, 1 << 24, n - 1]
+    runs = [(t, at[-1 - k], 0, k, 7) for k, t in enumerate(at)]
+    r = avl.trajectories_batched(dems, masks, 5.0, avl.params_tensor([p], "cuda"), avl.runs_tensor(runs, "cuda"), 3, 40)
+    for k, (t, s, _, run_id, seed) in enumerate(runs):
+        ref = oracle.trajectories(dems[t].cpu().numpy(), masks[s].cpu().numpy(), 5.0, oracle.make_params(**p), 3, 40, seed, run_id)
+        assert np.array_equal(r.counts[k].cpu().numpy(), ref.counts), k
+        assert list(r.stats[k].cpu().numpy()) == [ref.steps, ref.n_exit, ref.n_stop, ref.n_limit], k
+    del dems, masks, r
+    torch.cuda.empty_cache()
