@@ -3,7 +3,7 @@
 // per coded texel) with the start state of each, and the run table.
 //
 // A small pass is over in some 150 us, so launches count: these parts were ten kernels of 3 to 5 us each. They are
-// three, or two up to kDirectScan blocks of mask: one for everything that depends on the call's inputs alone (its
+// three, or two where the masks are small (kDirectScan): one for everything that depends on the call's inputs alone (its
 // blocks take one of three roles), a scan of the mask counts where there are many, and one that writes the cells and
 // their records and, for a single run, the run table. All of them are streaming passes.
 #include <algorithm>
@@ -158,7 +158,7 @@ hipError_t launch_prepare(PrepArgs a, hipStream_t s) {
         a.fill_blocks[k] = (uint32_t)nb;
         total += nb;
     }
-    // a launch holds less than 2^32 threads, and a batch of very many small tiles or masks has a block for each; its entry
+    // a launch holds less than 2^32 threads (more wrap, without an error), and a batch of very many small tiles or masks has a block for each; its entry
     // limits keep the blocks of all roles below 2^32
     constexpr uint64_t kMaxBlocks = uint64_t(1) << 23;
     hipError_t e = hipSuccess;
@@ -171,9 +171,8 @@ hipError_t launch_prepare(PrepArgs a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------------------------------ scan of the counts
-// Block m: exclusive scan of mask m's nb counts in place, its total into n_cells[m]. Only for masks of more than
-// kDirectScan chunks: up to there every block of the next kernel sums the counts before its own itself (at most 8
-// loads a thread from L2).
+// Block m: exclusive scan of mask m's nb counts in place, its total into n_cells[m]. Only where there are many
+// (kDirectScan): else every block of the next kernel sums the counts before its own itself.
 __global__ __launch_bounds__(1024) void k_scan_counts(uint32_t* __restrict__ blk, uint32_t nb, int32_t* __restrict__ n_cells) {
     __shared__ uint32_t wsum[1024 / kWave];
     uint32_t* const p = blk + (uint64_t)blockIdx.x * nb;
@@ -253,14 +252,18 @@ __global__ __launch_bounds__(kScanThreads) void k_release_list(ListArgs a) {
     }
 }
 
-// nb up to which the list's blocks sum the counts before them themselves instead of a scan of its own: at 2048 chunks
-// (8 M texels) that is 4 loads a thread on average, 17 MB from L2 in all, under the 4 us of a launch.
-constexpr uint32_t kDirectScan = 2048;
+// Chunks of one mask up to which the list's blocks sum the counts before them themselves instead of a scan of its own. Those
+// sums read nb^2 / 2 counts a mask (at 2048 chunks, 8 M texels: 4 loads a thread on average, 8.4 MB from L2 in all), the scan
+// costs a launch; so for several masks nb^2 times their number decides. A batch with nothing else to do, summed and scanned: one
+// mask of 1024 chunks 42.4 and 44.0 us, of 2048 53.4 and 55.1, of 4096 82.1 and 81.7; 4 of 1024 48.7 and 49.4, 16 of 1024 74.7 and
+// 71.1, 64 of 1024 186 and 161; 4 of 2048 66.4 and 65.4, 64 of 2048 390 and 298. Up to kScanThreads chunks a thread reads one
+// count at most and a scan never pays (64 of 256 66.6 and 65.0, 16 of 256 40.2 and 41.2); that also bounds the scan's grid.
+constexpr uint64_t kDirectScan = 2048;
 
 hipError_t launch_release_list(ListArgs a, uint32_t n_masks, hipStream_t s) {
     a.nb = (uint32_t)scan_blocks(a.n);
     if (a.nb == 0) return hipErrorInvalidValue;
-    a.scanned = a.nb > kDirectScan ? 1 : 0;
+    a.scanned = a.nb > (uint32_t)kScanThreads && (uint64_t)a.nb * a.nb * n_masks > kDirectScan * kDirectScan ? 1 : 0;
     if (a.scanned) hipLaunchKernelGGL(k_scan_counts, dim3(n_masks), dim3(1024), 0, s, a.blk, a.nb, a.n_cells);
     for (uint32_t m = 0; m < n_masks; m += 65535u) {  // the grid's y limit
         ListArgs c = a;

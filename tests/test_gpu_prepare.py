@@ -74,3 +74,25 @@ def test_batch_of_more_small_tiles_than_one_launch_holds(avl):
         assert list(r.stats[k].cpu().numpy()) == [ref.steps, ref.n_exit, ref.n_stop, ref.n_limit], k
     del dems, masks, r
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("shape,n_masks", [((2897, 2897), 2), ((2048, 4096), 2), ((1024, 1028), 63),
+                                           ((1024, 1028), 64), ((512, 2048), 66)])
+def test_batch_of_large_sparse_masks(avl, shape, n_masks):
+    # several masks with and without a scan of their counts: a run of each equals the plain call
+    rng = np.random.default_rng(n_masks)
+    dem = torch.from_numpy((rng.random(shape) * 15.0).astype(np.float32)).cuda()[None]
+    masks = torch.zeros((n_masks, *shape), dtype=torch.uint8, device="cuda")
+    for s in range(n_masks):  # few cells, first and last texel of every third mask among them
+        at = np.concatenate([rng.integers(0, dem.numel(), 40 + s), [0, dem.numel() - 1] if s % 3 == 0 else []]).astype(np.int64)
+        masks[s].view(-1)[torch.from_numpy(at).cuda()] = 1
+    p = dict(synth.DEFAULT_PARAMS, mu=0.1)
+    used = [0, 1, n_masks // 2, n_masks - 1]
+    r = avl.trajectories_batched(dem, masks, 5.0, avl.params_tensor([p], "cuda"),
+                                 avl.runs_tensor([(0, s, 0, k, 19) for k, s in enumerate(used)], "cuda"), 5, 60)
+    for k, s in enumerate(used):
+        one = avl.trajectories(dem[0], masks[s], 5.0, avl.Params.make(**p), 5, 60, 19, run_id=k)
+        assert int(one.counts.view(torch.int32).sum()) > 0
+        assert torch.equal(r.counts[k].view(torch.int32), one.counts.view(torch.int32)), s
+        assert torch.equal(r.vmax[k], one.vmax), s
+        assert torch.equal(r.stats[k].view(torch.int64), one.stats.view(torch.int64)), s
