@@ -117,7 +117,7 @@ struct TrajArgs {
     uint32_t n_runs;
     uint32_t S;                                  // step limit
     float g2;                                    // 2g
-    const StartRec* __restrict__ starts;         // single run: one per release cell; batched: NULL
+    const StartRec* __restrict__ starts;         // one per release cell (batch: per scenario, on its first run's tile)
     DivU32 pdiv;                                 // division by the particles per cell (same for every run)
     const float* __restrict__ dem_pad;           // the DEM tiles with a replicated border, (H + 2)(W + 2) each
     uint32_t pad_bytes;                          // bytes of one padded tile, (H + 2) (W + 2) x 4 < 2^32
@@ -245,7 +245,7 @@ hipError_t launch_batch_records(const RunSpec* specs, const int32_t* rec_run, co
                                 uint32_t n_scen, const int32_t* cells, const float* dem_pad, int32_t H, int32_t W,
                                 StartRec* starts, hipStream_t s);
 hipError_t launch_trajectories(const TrajArgs& a, bool batched, const LaunchShape& shape, hipStream_t s);
-// The recording instantiation (single run, variant 0's shape, runout-angle stop compiled in).
+// The recording instantiation (single run, runout-angle stop compiled in; a shape of its own: 1024 threads, eight slots per lane).
 hipError_t launch_trajectories_record(const TrajArgs& a, hipStream_t s);
 
 // Memory microbenchmarks (membench.hip): the wave-order schedule of a recorded pass's gathers and cell visits,
@@ -294,8 +294,8 @@ struct SmoothArgs {
 size_t smooth_checkpoints(uint32_t S);
 size_t smooth_scratch_bytes();
 size_t smooth_reduce_blocks(unsigned long long cap);
-// Kernel variants of the smooth forward and of the adjoint (grid shapes only: every variant gives the same
-// results); the library's tuner picks one per problem size.
+// Kernel variants of the smooth forward (grid shapes, with the velocity raster also where its splats go first) and of the
+// adjoint (sort windows): every variant gives the same results; the library's tuner picks one per problem size.
 int smooth_forward_variants(bool velocity = true, uint32_t P = 1);  // those that differ for such a pass
 int smooth_backward_variants();
 hipError_t launch_smooth_forward(const SmoothArgs& a, int variant, hipStream_t s);
@@ -345,7 +345,7 @@ hipError_t launch_finalize_vmax(uint32_t* vmax_bits, int64_t n, hipStream_t s);
 // Persistent-grid shape of kernel variant `variant` on the current device; number of variants.
 LaunchShape trajectory_shape(bool batched, int variant);
 int trajectory_variants();
-// info[0..7]: threads per block, iterations per epoch, table slots, probes, window top-up (x block), retention
+// info[0..7]: threads per block, iterations per epoch, table slots, candidate slots per key, window top-up (x block), retention
 // threshold, waves per SIMD of the register budget, slots per lane; false for an index out of range.
 bool trajectory_variant_info(int variant, int32_t* info);
 

@@ -27,7 +27,9 @@ static_assert(kPrepThreads == kScanThreads, "the counting role scans with the bl
 typedef uint32_t u32x4a4 __attribute__((ext_vector_type(4), aligned(4)));  // 16 bytes at a 4-byte aligned address
 }  // namespace
 
-// exclusive scan of one value per thread over a block of kScanThreads; returns the block total in *total
+// exclusive scan of one value per thread over a block of kScanThreads; returns the block total in *total. kAgain: another one
+// follows in the block.
+template <bool kAgain>
 __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t* total) {
     __shared__ uint32_t wsum[kScanThreads / kWave];
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
@@ -40,7 +42,7 @@ __device__ inline uint32_t block_excl_scan(uint32_t v, uint32_t* total) {
         before += (k < wid) ? wsum[k] : 0u;
         tot += wsum[k];
     }
-    __syncthreads();
+    if (kAgain) __syncthreads();
     *total = tot;
     return before + inc - v;
 }
@@ -116,7 +118,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_prepare(PrepArgs a) {
         const uint32_t m = b / a.nb, chunk = b - m * a.nb;
         const int64_t base = (int64_t)chunk * kScanChunk + (int64_t)threadIdx.x * kScanPerThread;
         uint32_t total;
-        (void)block_excl_scan(count16(mask16(a.mask + (int64_t)m * a.n, base, a.n)), &total);
+        (void)block_excl_scan<false>(count16(mask16(a.mask + (int64_t)m * a.n, base, a.n)), &total);
         if (threadIdx.x == 0) a.blk[b] = total;
         return;
     }
@@ -213,28 +215,26 @@ __global__ __launch_bounds__(1024) void k_scan_counts(uint32_t* __restrict__ blk
 // chunk's block knows the mask's total: n_cells, and a single run's table.
 __global__ __launch_bounds__(kScanThreads) void k_release_list(ListArgs a) {
     __shared__ uint16_t list[kScanChunk];
-    __shared__ uint32_t sh_base;
     const uint32_t m = blockIdx.y, b = blockIdx.x;
     const uint8_t* const mask = a.mask + (int64_t)m * a.n;
     const int64_t chunk = (int64_t)b * kScanChunk;
     const uint4 w4 = mask16(mask, chunk + (int64_t)threadIdx.x * kScanPerThread, a.n);
     const uint32_t* const blk = a.blk + (uint64_t)m * a.nb;
-    uint32_t total;
+    uint32_t base, total;
     if (a.scanned) {
-        if (threadIdx.x == 0) sh_base = blk[b];
+        base = blk[b];
     } else {
         uint32_t sum = 0;
         for (uint32_t i = threadIdx.x; i < b; i += kScanThreads) sum += blk[i];
-        (void)block_excl_scan(sum, &total);
-        if (threadIdx.x == 0) sh_base = total;
+        (void)block_excl_scan<true>(sum, &base);
     }
-    uint32_t pos = block_excl_scan(count16(w4), &total);  // its barriers publish sh_base too
+    uint32_t pos = block_excl_scan<false>(count16(w4), &total);
     const uint32_t w[4] = {nonzero_bytes(w4.x), nonzero_bytes(w4.y), nonzero_bytes(w4.z), nonzero_bytes(w4.w)};
 #pragma unroll
-    for (int k = 0; k < kScanPerThread; ++k)  // bytes past n were read as 0
-        if ((w[k >> 2] >> (8 * (k & 3) + 7)) & 1u) list[pos++] = (uint16_t)(threadIdx.x * kScanPerThread + k);
+    for (int q = 0; q < 4; ++q)  // bytes past n were read as 0
+        for (uint32_t v = w[q]; v != 0u; v &= v - 1u)
+            list[pos++] = (uint16_t)(threadIdx.x * kScanPerThread + 4 * q + (__builtin_ctz(v) >> 3));
     __syncthreads();
-    const uint32_t base = sh_base;
     int32_t* const cells = a.cells + (int64_t)m * a.cells_stride;
     for (uint32_t i = threadIdx.x; i < total; i += kScanThreads) {
         const uint32_t cell = (uint32_t)(chunk + list[i]);

@@ -140,9 +140,8 @@ void k_trajectories(TrajArgs a) {
     const int lane = threadIdx.x & (kWave - 1);
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
     const uint64_t total = wave_bcast64(a.run_off[a.n_runs]);
-    // A small problem runs on fewer blocks: with ~1 particle per lane every wave would issue the whole
-    // iteration for a few live lanes, and the waves of a SIMD would share its issue slots until the
-    // longest path ends. Blocks past what gives each lane about the variant's slots per lane leave at once.
+    // A small problem runs on fewer blocks: those past what gives each lane about the variant's slots per lane leave at
+    // once.
     const uint64_t active = min((uint64_t)gridDim.x, active_blocks(total, kBlock, a.slots_per_lane));
     if ((uint64_t)blockIdx.x >= active) return;
     const int W = a.W, H = a.H;
@@ -744,7 +743,7 @@ struct Variant {
     const void* batch;
     int block;
     uint32_t spl;  // particle slots per lane that size the grid of a small problem
-    int shape[7];  // block, iterations per epoch, table slots, probes, window, retention, waves per SIMD
+    int shape[7];  // block, iterations per epoch, table slots, candidate slots, window, retention, waves per SIMD
     void (*launch_single)(dim3, dim3, hipStream_t, const TrajArgs&);        // runout-angle stop compiled in
     void (*launch_single_plain)(dim3, dim3, hipStream_t, const TrajArgs&);  // without it
     void (*launch_batch)(dim3, dim3, hipStream_t, const TrajArgs&);
