@@ -115,7 +115,7 @@ __device__ __forceinline__ void fill_role(const Fill& f, uint32_t block) {
 __global__ __launch_bounds__(kPrepThreads) void k_prepare(PrepArgs a) {
     uint32_t b = a.first + blockIdx.x;
     if (b < a.count_blocks) {
-        const uint32_t m = b / a.nb, chunk = b - m * a.nb;
+        const uint32_t m = a.n_masks == 1u ? 0u : b / a.nb, chunk = b - m * a.nb;
         const int64_t base = (int64_t)chunk * kScanChunk + (int64_t)threadIdx.x * kScanPerThread;
         uint32_t total;
         (void)block_excl_scan<false>(count16(mask16(a.mask + (int64_t)m * a.n, base, a.n)), &total);
@@ -180,11 +180,16 @@ __global__ __launch_bounds__(1024) void k_scan_counts(uint32_t* __restrict__ blk
     uint32_t* const p = blk + (uint64_t)blockIdx.x * nb;
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
     uint32_t carry = 0;
+    uint32_t v[4], next[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; ++k) next[k] = threadIdx.x * 4u + k < nb ? p[threadIdx.x * 4u + k] : 0u;
     for (uint32_t base = 0; base < nb; base += 4096u) {
         const uint32_t i0 = base + threadIdx.x * 4u;
-        uint32_t v[4];
 #pragma unroll
-        for (uint32_t k = 0; k < 4u; ++k) v[k] = i0 + k < nb ? p[i0 + k] : 0u;
+        for (uint32_t k = 0; k < 4u; ++k) {
+            v[k] = next[k];
+            next[k] = i0 + 4096u + k < nb ? p[i0 + 4096u + k] : 0u;
+        }
         const uint32_t local = v[0] + v[1] + v[2] + v[3];
         const uint32_t inc = wave_incl_scan(local);
         if (lane == kWave - 1) wsum[wid] = inc;
