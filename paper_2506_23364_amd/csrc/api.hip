@@ -1039,8 +1039,8 @@ avl::SetupOne setup_of(const avl::SmoothWs& sw, const avl_params& p, float cell_
 // The smooth forward pass. `prepared`: the workspace already holds this mask's release cells, padded DEM,
 // start records and per-particle masses from an earlier pass with the same DEM, mask, mass and particles per
 // cell (a calibration loop, where only the friction parameters change between passes), and the run constants, cleared
-// rasters, counters and queues from the end of that loop's previous iteration. `p_dev`, `spec_dev` (nullable, together): the run constants are set up from
-// these device copies of the parameters and the run (a loop that updates the parameters on the device);
+// rasters, counters and queues from the end of that loop's previous iteration. `p_dev`, `spec_dev` (nullable, together):
+// the run constants are set up from these device copies of the parameters and the run (a loop that updates the parameters on the device);
 // `params` then serves only for the host checks of the parameters the loop does not change.
 int smooth_forward(const float* dem, const uint8_t* mask, const float* mass, int32_t H, int32_t W,
                    float cell_size, const avl_params* params, uint32_t particles_per_cell,

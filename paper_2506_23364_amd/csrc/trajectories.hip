@@ -768,7 +768,9 @@ constexpr Variant make_variant(uint32_t spl = (uint32_t)kSlotsPerLane) {
 // slots per lane that size a small problem's grid. 1024-thread blocks run two per CU at eight waves per SIMD
 // (64 VGPRs; 6144 slots of 12 bytes are 72 KiB of LDS per block); the 768- and 512-thread shapes run at six
 // (80 VGPRs), two and three blocks per CU, and the 384-thread shape at six with four blocks per CU. The fifth
-// keeps no slot across epochs.
+// keeps no slot across epochs. The 1024-thread shapes spill up to 24 bytes a lane since the steps run in pairs, and lose where the
+// chip is full (8192^2 13.9 to 18.4 ms against 12.7 to 13.0 of the best six-wave shapes, 2048^2 tile 2.85 to 3.15 against 2.69,
+// 1024-run ensemble 26.7 to 30.8 against 24.6); in between one of them is kept now and then (release texture of 2 x 2 texels, 1001 x 1203).
 // A problem that does not fill the chip lasts as long as a lane's paths, so one slot per lane is best for it (first
 // shape: 314,576 paths of 130 steps 0.60 ms, at two slots per lane 1.04, at eight 2.4; 30,000 paths of 11 steps 0.13,
 // 0.19 and 0.31 ms), and one that fills it does not see the difference. The first shape is the fastest, or within a
